@@ -203,8 +203,9 @@ int lede_set_verify_reuse(lede_ctx* ctx, int32_t enable);
 
 /* Prefill (the paper does not describe it; decoding in Section 4.1 starts
  * from a prompt at batch 1): append n prompt tokens (host int32, each in
- * [0, vocab)) at positions seq_len .. seq_len+n-1 through all L layers in
- * 16-row passes of the verify kernels, writing their K/V; the full model's
+ * [0, vocab)) at positions seq_len .. seq_len+n-1 through all L layers,
+ * writing their K/V, in passes of up to 2048 rows whose results are bit for
+ * bit those of the verify kernels; the full model's
  * argmax at the last row becomes the pending token and is returned in
  * *next_token (host), and its -log max p enters the confidence trace.
  * Valid when no draft is outstanding (LEDE_E_STATE); LEDE_E_ARG on a null

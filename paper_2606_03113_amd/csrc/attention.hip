@@ -1,5 +1,6 @@
 // Split-KV attention over the paged KV cache (gfx950).
 #include "device.h"
+#include "wide.h"
 
 namespace lede {
 
@@ -202,7 +203,10 @@ __global__ __launch_bounds__(HD * COMBINE_GROUPS) void k_attn_combine(AttnArgs a
   __syncthreads();
   if (sg == 0) {
     for (int q = 1; q < S && q * B < nc; ++q) fold_step(mx, l, acc, st[q][0][i], st[q][1][i], st[q][2][i]);
-    Elem<DT>::store(a.out, (size_t)m * a.ldo + head * HD + i, acc / l);
+    if (a.KT_tiled)
+      Elem<DT>::store((uint8_t*)a.out + tiled_row_off<DT>(m, head * HD + i, a.KT_tiled), 0, acc / l);
+    else
+      Elem<DT>::store(a.out, (size_t)m * a.ldo + head * HD + i, acc / l);
   }
 }
 

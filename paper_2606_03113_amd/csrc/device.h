@@ -100,6 +100,20 @@ __device__ __forceinline__ uint4 ld16_stream(const void* p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)p));
 }
 
+// The rotary pair of (x0, x1): (x0 cos - x1 sin, x0 sin + x1 cos), each one
+// rounded product and one fused step, so that every kernel rounds alike.
+__device__ __forceinline__ float2 rope_pair(float x0, float x1, float2 cs) {
+  return make_float2(fmaf(x0, cs.x, -(x1 * cs.y)), fmaf(x0, cs.y, x1 * cs.x));
+}
+
+// 16 bytes from LDS through an LDS-typed pointer: a select between such a
+// load and a register constant cannot become a load through a selected
+// pointer (which would put the constant in scratch memory).
+__device__ __forceinline__ uint4 lds_ld16(const uint8_t* p) {
+  const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)p;
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // ---- row access --------------------------------------------------------------
 
 __device__ __forceinline__ float bf16lo(uint32_t u) { return __uint_as_float(u << 16); }

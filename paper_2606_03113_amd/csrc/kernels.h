@@ -17,6 +17,7 @@ struct NormArgs {
   int embed; const void* embed_w; TokenSrc tok;  // h[m] = embed[tok(m)] first
   int vocab;
   void* x;                 // output rows
+  int KT_tiled;            // > 0: tiled output rows (wide.h) of this many tiles
   int f32_out;             // 1: fp32 output, not rounded
   uint64_t* zero_keys; int n_zero_keys;
 };
@@ -31,6 +32,7 @@ struct AttnArgs {
   int max_chunks;
   float* part;                     // [M][nq][max_chunks][hd + 2]
   void* out; int ldo;              // combine output [M][nq*hd], model dtype
+  int KT_tiled;                    // > 0: tiled output rows (wide.h) of this many tiles
   int mfma;                        // bf16: partials on the matrix cores (rows of verify, prefill, AR)
 };
 

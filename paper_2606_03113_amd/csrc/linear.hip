@@ -138,16 +138,15 @@ __device__ __forceinline__ void epilogue(const LinearArgs& a, int g, float (*ct)
             const int pos = c + m;
             const float2 cs = p.cs;
             const float x0 = ct[r][m], x1 = ct[r + 8][m];
-            const float y0 = x0 * cs.x - x1 * cs.y;
-            const float y1 = x1 * cs.x + x0 * cs.y;
+            const float2 y = rope_pair(x0, x1, cs);
             if (isq) {
               float* q = a.q + (size_t)m * a.ldq + head * hd;
-              q[i] = y0;
-              q[i + hd / 2] = y1;
+              q[i] = y.x;
+              q[i + hd / 2] = y.y;
             } else {
               const size_t base = ((((size_t)a.layer * a.n_pages + p.page) * a.nkv + head) * 64 + (pos & 63)) * hd;
-              Elem<DT>::store(a.kcache, base + i, y0);
-              Elem<DT>::store(a.kcache, base + i + hd / 2, y1);
+              Elem<DT>::store(a.kcache, base + i, y.x);
+              Elem<DT>::store(a.kcache, base + i + hd / 2, y.y);
             }
           }
         }
@@ -187,15 +186,6 @@ __device__ __forceinline__ void epilogue(const LinearArgs& a, int g, float (*ct)
       break;
     }
   }
-}
-
-
-// 16 bytes from LDS through an LDS-typed pointer: a select between such a
-// load and a register constant cannot become a load through a selected
-// pointer (which would put the constant in scratch memory).
-__device__ __forceinline__ uint4 lds_ld16(const uint8_t* p) {
-  const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)p;
-  return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // Deterministic sum over the NW wavefronts of a block (every thread takes

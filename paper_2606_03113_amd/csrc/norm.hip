@@ -1,5 +1,6 @@
 // RMSNorm rows of the verify / prefill path and the Q-network state (gfx950).
 #include "device.h"
+#include "wide.h"
 
 namespace lede {
 
@@ -74,6 +75,7 @@ __global__ __launch_bounds__(256) void k_norm(NormArgs a) {
       y.w = (v[j].w * inv) * g[j].w;
       if (a.embed) *(float4*)(h + i) = v[j];
       if (a.f32_out) store4<0>(out, i, y);
+      else if (a.KT_tiled) store4<DT>((uint8_t*)a.x + tiled_row_off<DT>(m, i, a.KT_tiled), 0, y);
       else store4<DT>(out, i, y);
     }
   }

@@ -16,6 +16,7 @@
 #include "../../include/lede.h"
 #include "ctx_view.h"
 #include "kernels.h"
+#include "wide.h"
 
 using namespace lede;
 
@@ -23,6 +24,7 @@ namespace {
 
 constexpr int PAGE = 64;
 constexpr int MROWS = 16;   // rows of one verify / prefill pass
+constexpr int WIDE_ROWS = 2048;  // rows of one prefill pass of the many-row kernels, at most
 static_assert(MROWS <= KEY_PITCH && 15 + 2 <= KEY_PITCH, "a key buffer holds every row's key and every draft's");
 constexpr int RECORD_INTS = 64;
 constexpr int UNIF_FLOATS = 2 * SAMPLE_SLOTS + 1;  // uniforms of a sampled step
@@ -40,6 +42,9 @@ struct Layout {
   // workspace offsets
   size_t h, xn, ss, q, attn_out, act, part, logits, gstats, dkeys, vkeys, qs, qhid, qv, seq_len, btab, prompt,
       record, rope, unif, dstats, trace, trace_state, trace_bak, pol_out, wsbytes;
+  // rows of a many-row prefill pass (wide_rows of them; the rest as h .. act, row inputs tiled)
+  int wide_rows;
+  size_t wh, wxn, wss, winv, wq, wattn, wact;
   size_t kvbytes, kv_half;
 };
 
@@ -134,6 +139,15 @@ Layout make_layout(const lede_config* c) {
   o.trace_state = take(4 * 4);
   o.trace_bak = take((POLICY_TRACE + 2) * 4);
   o.pol_out = take((size_t)(c->n_exits + POLICY_MAX_DRAFT) * POLICY_LOG * 4);
+  o.wide_rows = std::min(WIDE_ROWS, (o.max_ctx + WIDE_ROW_PAD - 1) / WIDE_ROW_PAD * WIDE_ROW_PAD);
+  const size_t wr = o.wide_rows;
+  o.wh = take(wr * o.d * 4);
+  o.wxn = take(wr / 16 * k_tiles(o.dt, o.d) * TILE_BYTES);
+  o.wss = take(wr * (o.d / 16) * 4);
+  o.winv = take(wr * 4);
+  o.wq = take(wr * o.qd * 4);
+  o.wattn = take(wr / 16 * k_tiles(o.dt, o.qd) * TILE_BYTES);
+  o.wact = take(wr / 16 * k_tiles(o.dt, o.F) * TILE_BYTES);
   o.wsbytes = off;
 
   o.kv_half = align256((size_t)o.L * o.n_pages * o.nkv * PAGE * o.hd * o.es);
@@ -491,6 +505,32 @@ LinearArgs base_linear(const lede_ctx* c) {
   return a;
 }
 
+// Attention of M <= 16 rows at positions seq_len + pos_off + m of layer j
+// (the caller sets the query and output rows).
+AttnArgs attn_args(const lede_ctx* c, int j, int M, bool vec, int pos_off) {
+  const Layout& o = c->lo;
+  AttnArgs at{};
+  at.ldq = o.qd;
+  at.kcache = c->kv; at.vcache = c->kv + o.kv_half;
+  at.layer = j; at.n_pages = o.n_pages; at.nq = o.nq; at.nkv = o.nkv; at.hd = o.hd; at.M = M;
+  at.block_table = c->S<int32_t>(o.btab); at.seq_len = c->S<int32_t>(o.seq_len); at.pos_off = pos_off;
+  const int G = o.nq / o.nkv;
+  at.rows_per_block = std::min(16, M * G);
+  const int n_rs = (M * G + at.rows_per_block - 1) / at.rows_per_block;
+  // about 2048 blocks, one page each where the context allows: at 4096
+  // positions (13B shape, 65 pages per head) 16.05 against 16.32 ms per
+  // step with 512 blocks of five pages; shorter contexts have a page per
+  // block either way
+  at.n_split = std::max(1, std::min(o.max_chunks, (2048 + o.nkv * n_rs - 1) / (o.nkv * n_rs)));
+  at.max_chunks = o.max_chunks;
+  at.part = c->S<float>(o.part);
+  // bf16 partials on the matrix cores for every multi-row pass (verify,
+  // autoregressive, prefill: one kernel whatever the row count, so a row's
+  // bits do not depend on it) and for one-row passes with grouped heads
+  at.mfma = o.dt == 1 && (!vec || G > 1);
+  return at;
+}
+
 // Run rows [0, M) at positions seq_len + pos_off + m through layers
 // [l_begin, l_end).  Vector kernels for one row (draft path), matrix-core
 // kernels otherwise.  qnet_after: run the Q-network after this many layers
@@ -543,26 +583,9 @@ int run_layers(lede_ctx* c, int M, bool vec, TokenSrc tok, int pos_off, int l_be
     }
     LAUNCH_LINEAR(vec, qa, dt);
 
-    AttnArgs at{};
-    at.q = c->S<float>(o.q); at.ldq = o.qd;
-    at.kcache = c->kv; at.vcache = c->kv + o.kv_half;
-    at.layer = j; at.n_pages = o.n_pages; at.nq = o.nq; at.nkv = o.nkv; at.hd = o.hd; at.M = M;
-    at.block_table = c->S<int32_t>(o.btab); at.seq_len = c->S<int32_t>(o.seq_len); at.pos_off = pos_off;
-    const int G = o.nq / o.nkv;
-    at.rows_per_block = std::min(16, M * G);
-    const int n_rs = (M * G + at.rows_per_block - 1) / at.rows_per_block;
-    // about 2048 blocks, one page each where the context allows: at 4096
-    // positions (13B shape, 65 pages per head) 16.05 against 16.32 ms per
-    // step with 512 blocks of five pages; shorter contexts have a page per
-    // block either way
-    at.n_split = std::max(1, std::min(o.max_chunks, (2048 + o.nkv * n_rs - 1) / (o.nkv * n_rs)));
-    at.max_chunks = o.max_chunks;
-    at.part = c->S<float>(o.part);
+    AttnArgs at = attn_args(c, j, M, vec, pos_off);
+    at.q = c->S<float>(o.q);
     at.out = c->S<void>(o.attn_out); at.ldo = o.qd;
-    // bf16 partials on the matrix cores for every multi-row pass (verify,
-    // autoregressive, prefill: one kernel whatever the row count, so a row's
-    // bits do not depend on it) and for one-row passes with grouped heads
-    at.mfma = dt == 1 && (!vec || G > 1);
     const double n_pos = (double)c->seq_len + pos_off + M;
     LAUNCH(LEDE_K_ATTENTION, n_pos * o.kvd * 2.0 * o.es + 2.0 * M * o.qd * 4,
            launch_attention(dt, at, s));
@@ -640,6 +663,93 @@ int run_layers(lede_ctx* c, int M, bool vec, TokenSrc tok, int pos_off, int l_be
   // a one-row pass's last down projection prepared the final norm's split
   // for its row (a multi-row pass's head reads it through its `split` flag)
   if (vec && l_end > l_begin) c->split_row = vec_row;
+  return LEDE_OK;
+}
+
+// Prefill rows [0, M), 16 < M <= wide_rows, at positions seq_len + pos_off + m
+// through every layer with the many-row kernels.  Bit for bit the passes of
+// 16 rows that run_layers would take.  head: leave the last row group's rows
+// (1..16 of them) and their final-norm sums where run_head reads them, and
+// clear its keys.
+int run_wide(lede_ctx* c, int M, const int32_t* tokens, int pos_off, bool head, uint64_t* keys, hipStream_t s) {
+  const Layout& o = c->lo;
+  const int dt = o.dt, KTd = k_tiles(dt, o.d), KTq = k_tiles(dt, o.qd), KTf = k_tiles(dt, o.F);
+  c->split_row = -1;
+  float* h = c->S<float>(o.wh);
+  uint8_t* xn = c->S<uint8_t>(o.wxn);
+  auto bytes = [&](const WideArgs& a) {
+    return (double)a.n_groups * 16 * a.K * o.es + (double)M * (a.K * o.es + a.n_groups * 16.0 * (a.epi == EPI_RESID ? 8 : 4));
+  };
+  auto base = [&](size_t w, int n_groups, int KT, int K, int epi, const void* x) {
+    WideArgs a{};
+    a.w = c->W<uint8_t>(w); a.n_groups = n_groups; a.KT = KT; a.K = K; a.M = M; a.epi = epi;
+    a.x = (const uint8_t*)x;
+    return a;
+  };
+  // the scale of a split norm's consumer
+  auto inv = [&](WideArgs& a) -> int {
+    RowInvArgs ra{};
+    ra.ss = c->S<float>(o.wss); ra.groups = o.d / 16; ra.M = M; ra.K = o.d; ra.eps = c->cfg.rms_eps;
+    ra.inv = c->S<float>(o.winv);
+    LAUNCH(LEDE_K_NORM, (double)M * (o.d / 16) * 4, launch_row_inv(ra, s));
+    a.inv = ra.inv;
+    return LEDE_OK;
+  };
+  auto produce = [&](WideArgs& a, const void* gain) {
+    a.h = h; a.ldh = o.d;
+    if (!gain) return;
+    a.ss_out = c->S<float>(o.wss); a.xg_gain = gain; a.xg = xn; a.KT_out = KTd;
+  };
+  for (int j = 0; j < o.L; ++j) {
+    const auto& lw = o.lay[j];
+    WideArgs qa = base(lw.wqkv, (o.qd + 2 * o.kvd) / 16, KTd, o.d, EPI_QKV, xn);
+    if (j == 0) {
+      NormArgs na{};
+      na.M = M; na.d = o.d; na.ldh = o.d; na.ldx = o.d;
+      na.h = h; na.gain = c->W<void>(lw.attn_norm); na.eps = c->cfg.rms_eps;
+      na.embed = 1; na.embed_w = c->W<void>(o.embed); na.tok = TokenSrc{tokens, nullptr}; na.vocab = o.V;
+      na.x = xn; na.KT_tiled = KTd;
+      if (head) { na.zero_keys = keys; na.n_zero_keys = MROWS; }
+      LAUNCH(LEDE_K_NORM, (double)M * o.d * (4 + o.es), launch_norm(dt, na, s));
+    } else if (int rc = inv(qa)) {
+      return rc;
+    }
+    qa.q = c->S<float>(o.wq); qa.ldq = o.qd;
+    qa.kcache = c->kv; qa.vcache = c->kv + o.kv_half;
+    qa.layer = j; qa.n_pages = o.n_pages; qa.nq = o.nq; qa.nkv = o.nkv; qa.hd = o.hd;
+    qa.block_table = c->S<int32_t>(o.btab); qa.seq_len = c->S<int32_t>(o.seq_len); qa.pos_off = pos_off;
+    qa.rope = c->S<float2>(o.rope);
+    LAUNCH(LEDE_K_LINEAR_MFMA, bytes(qa), launch_wide(dt, qa, s));
+
+    for (int r = 0; r < M; r += MROWS) {
+      const int m = std::min(MROWS, M - r);
+      AttnArgs at = attn_args(c, j, m, false, pos_off + r);
+      at.q = c->S<float>(o.wq) + (size_t)r * o.qd;
+      at.out = c->S<uint8_t>(o.wattn) + (size_t)(r / 16) * KTq * TILE_BYTES; at.KT_tiled = KTq;
+      const double n_pos = (double)c->seq_len + pos_off + r + m;
+      LAUNCH(LEDE_K_ATTENTION, n_pos * o.kvd * 2.0 * o.es + 2.0 * m * o.qd * 4, launch_attention(dt, at, s));
+    }
+
+    WideArgs oa = base(lw.wo, o.d / 16, KTq, o.qd, EPI_RESID, c->S<void>(o.wattn));
+    produce(oa, c->W<void>(lw.ffn_norm));
+    LAUNCH(LEDE_K_LINEAR_MFMA, bytes(oa), launch_wide(dt, oa, s));
+
+    WideArgs ga = base(lw.wgu, 2 * o.F / 16, KTd, o.d, EPI_SWIGLU, xn);
+    if (int rc = inv(ga)) return rc;
+    ga.act = c->S<void>(o.wact); ga.KT_out = KTf;
+    LAUNCH(LEDE_K_LINEAR_MFMA, bytes(ga), launch_wide(dt, ga, s));
+
+    WideArgs da = base(lw.wd, o.d / 16, KTf, o.F, EPI_RESID, c->S<void>(o.wact));
+    if (j + 1 < o.L) produce(da, c->W<void>(o.lay[j + 1].attn_norm));
+    else produce(da, head ? c->W<void>(o.final_norm) : nullptr);
+    LAUNCH(LEDE_K_LINEAR_MFMA, bytes(da), launch_wide(dt, da, s));
+  }
+  if (head) {
+    HeadRowsArgs ha{};
+    ha.x = xn; ha.KT = KTd; ha.r0 = (M - 1) / MROWS * MROWS; ha.n = M - ha.r0; ha.d = o.d;
+    ha.xn = c->S<void>(o.xn); ha.ss = c->S<float>(o.wss); ha.ss_out = c->S<float>(o.ss); ha.groups = o.d / 16;
+    LAUNCH(LEDE_K_NORM, (double)ha.n * o.d * 2 * o.es, launch_head_rows(dt, ha, s));
+  }
   return LEDE_OK;
 }
 
@@ -1124,19 +1234,21 @@ static int prefill_impl(lede_ctx* c, const int32_t* tokens, int32_t n, hipStream
   PRE();
   HIP_CHECK(c, hipMemcpyAsync(pd, tokens, (size_t)n * 4, hipMemcpyHostToDevice, s));
   uint64_t* vk = c->S<uint64_t>(c->lo.vkeys);
-  int last_m = 0;
-  for (int off = 0; off < n; off += MROWS) {
-    const int M = std::min(MROWS, n - off);
-    TokenSrc tok{pd + off, nullptr};
-    if ((rc = run_layers(c, M, false, tok, off, 0, c->lo.L, 0, vk, s))) return rc;
-    if (off + M == n) {
-      const bool trace = c->lo.He > 0;
-      if ((rc = run_head(c, M, false, vk, verify_logits(c, trace), s, 0, true))) return rc;
-      if (trace && (rc = push_trace(c, verify_logits(c, true) + (size_t)(M - 1) * c->lo.V, 1, nullptr, s)))
-        return rc;
-    }
-    last_m = M;
+  // passes of about equal size, whole row groups except the last
+  const int passes = (n + c->lo.wide_rows - 1) / c->lo.wide_rows;
+  const int rows = ((n + passes - 1) / passes + MROWS - 1) / MROWS * MROWS;
+  for (int off = 0; off < n; off += rows) {
+    const int M = std::min(rows, n - off);
+    // up to 16 rows the weight-streaming kernels are the faster ones
+    rc = M > MROWS ? run_wide(c, M, pd + off, off, off + M == n, vk, s)
+                   : run_layers(c, M, false, TokenSrc{pd + off, nullptr}, off, 0, c->lo.L, 0, vk, s);
+    if (rc) return rc;
   }
+  // the head and its logits: the last group of 16 rows
+  const int last_m = (n - 1) % MROWS + 1;
+  const bool trace = c->lo.He > 0;
+  if ((rc = run_head(c, last_m, false, vk, verify_logits(c, trace), s, 0, true))) return rc;
+  if (trace && (rc = push_trace(c, verify_logits(c, true) + (size_t)(last_m - 1) * c->lo.V, 1, nullptr, s))) return rc;
   c->last_rows = last_m;
   PRE();
   HIP_CHECK(c, hipMemcpyAsync(c->keys_h, vk, KEY_WORDS * 8, hipMemcpyDeviceToHost, s));

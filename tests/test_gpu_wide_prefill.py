@@ -1,0 +1,83 @@
+"""Prefill of more than 16 tokens runs the many-row kernels; up to 16 it runs
+the verify passes' kernels, which the oracle tests cover.  Both must leave the
+same bits: a prompt taken at once against the same prompt taken in pieces of
+at most 16 tokens, on the pages of a permuted pool, compared on the logits, the
+next token and the whole KV pool."""
+import numpy as np
+import pytest
+
+import lede_inputs as li
+from lede_inputs.configs import TINY, shrink
+from tests.parity import say
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+BF16_64 = shrink(TINY, name="bf16-hd64", dtype="bf16")
+BF16_128 = shrink(TINY, name="bf16-hd128", n_layers=3, d_model=512, n_heads=4, n_kv_heads=4, head_dim=128,
+                  ffn_dim=1376, vocab=4096, dtype="bf16", qnet_hidden=64, exits=(1, 2, 3))
+GQA_64 = shrink(TINY, name="bf16-gqa-hd64", n_layers=2, d_model=544, n_heads=6, n_kv_heads=2, head_dim=64,
+                ffn_dim=1000, vocab=2048, dtype="bf16", qnet_hidden=32, exits=(1, 2))
+GQA_128_F32 = shrink(TINY, name="f32-gqa-hd128", n_layers=2, d_model=512, n_heads=8, n_kv_heads=2, head_dim=128,
+                     ffn_dim=704, vocab=1024, dtype="f32", qnet_hidden=32, exits=(1, 2))
+GQA_8 = shrink(TINY, name="bf16-gqa8-hd128", n_layers=1, d_model=1024, n_heads=16, n_kv_heads=2, head_dim=128,
+               ffn_dim=1376, vocab=1024, dtype="bf16", qnet_hidden=32, exits=(1,))
+MODELS = [TINY, BF16_64, BF16_128, GQA_64, GQA_128_F32, GQA_8]
+# (tokens already cached, new tokens): one past a group, edges of row tiles and
+# pages, ragged ends, several page groups behind the rows
+SIZES = [(0, 17), (0, 64), (5, 65), (30, 127), (0, 129), (70, 300)]
+
+
+def _state(eng):
+    sl, pend, table = eng.lede_get_kv_state()
+    return sl, pend, table, eng.kv.cpu().numpy(), eng.logits(0)
+
+
+def _engine(model, max_ctx, seed):
+    from paper_2606_03113_amd import Engine
+    eng = Engine(model, max_ctx=max_ctx, k_max=8)
+    eng.kv.fill_(0xFF)  # NaNs in every slot that has not been written
+    eng.load_weights(li.weights(model), li.qnet_weights(model))
+    eng.lede_set_options(0, 1)
+    eng.lede_set_free_list(np.random.default_rng(seed).permutation(-(-max_ctx // 64)))
+    return eng
+
+
+def _check(model, max_ctx, ctx, n, piece=16):
+    toks = li.uniform_int(1, 20, ctx + n, 0, model.vocab - 1)
+    got = []
+    for step in (n, piece):
+        eng = _engine(model, max_ctx, ctx + n)
+        for i in range(0, ctx, 16):
+            eng.lede_prefill(toks[i:min(ctx, i + 16)])
+        for i in range(ctx, ctx + n, step):
+            eng.lede_prefill(toks[i:min(ctx + n, i + step)])
+        got.append(_state(eng))
+        eng.close()
+    (sl, pend, table, kv, z), (sl2, pend2, table2, kv2, z2) = got
+    assert (sl, pend, table) == (sl2, pend2, table2)
+    assert np.isfinite(z).all() and np.array_equal(z, z2)
+    assert np.array_equal(kv, kv2)
+
+
+@pytest.mark.parametrize("ctx,n", SIZES)
+@pytest.mark.parametrize("model", MODELS, ids=lambda m: m.name)
+def test_prefill_at_once_equals_pieces(model, ctx, n):
+    say("wide prefill", model.name, ctx, n)
+    _check(model, 448, ctx, n)
+
+
+@pytest.mark.parametrize("model", [BF16_64, GQA_64, TINY], ids=lambda m: m.name)
+def test_prefill_of_several_passes(model):
+    """More rows than one pass takes, ending in a ragged pass."""
+    say("wide prefill, several passes", model.name)
+    _check(model, 2400, 40, 2201)
+
+
+@pytest.mark.parametrize("n", [40, 200])
+def test_prefill_at_full_width(n):
+    """One layer at the Llama-2-7B widths."""
+    from lede_inputs.configs import WORKLOADS
+    m = shrink(WORKLOADS["llama2-7b"].model, n_layers=1, exits=(1,))
+    say("wide prefill, 7B widths", n)
+    _check(m, 512, 33, n)
