@@ -156,8 +156,8 @@ __device__ __forceinline__ void fold_step(float& mx, float& l, float& acc, float
   const float nm = fmaxf(mx, pm);
   const float so = (mx == -INFINITY) ? 0.f : __expf(mx - nm);
   const float sn = __expf(pm - nm);
-  l = l * so + pl * sn;
-  acc = acc * so + pa * sn;
+  l = fmaf(pl, sn, l * so);  // (spelled out: the kernels that fold must round alike)
+  acc = fmaf(pa, sn, acc * so);
   mx = nm;
 }
 
@@ -391,6 +391,223 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     }
     __syncthreads();  // the next page rewrites the staging
   }
+}
+
+// Attention of a prefill pass's rows (bf16 cache): 8 wavefronts of 16 query
+// rows walk a KV head's pages together, each page staged in LDS once for all
+// of them -- keys as matrix-core tiles (direct global-to-LDS copies), values
+// transposed -- while the next page is fetched.  A page's scores, maximum, sum
+// and weighted values are computed as in k_attn_mfma, and folded at once in
+// the order of k_attn_combine: pages in order within the runs of 16 that one
+// of its thread groups folds, then the groups in order.  So a row has the bits
+// of the two kernels at any row count, without their partials in memory.
+// Bound by the vector work beside the products (exponentials, the bf16 splits,
+// the fold): 2048 rows of the Llama-2-13B shape take 302 us a layer, against
+// 2180 for the two kernels 16 rows at a time; 97 rows 17 against 74.
+template <int HD>
+__global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
+  constexpr int KS = HD / 32, NT = HD / 16;  // k-steps of the scores, output tiles
+  constexpr int NW = 8, KT = 4 * KS;         // wavefronts, key tiles of a page
+  constexpr int VS = 36;                     // words between the dims of the transposed values (and rows of the weights)
+  extern __shared__ __align__(16) uint8_t smem[];
+  uint8_t* kb = smem;                                          // [2][KT][1 KiB]
+  uint32_t* vb = (uint32_t*)(smem + 2 * KT * 1024);            // [2][HD][VS]: token pairs of a dim
+  uint32_t* pb = vb + 2 * HD * VS;                             // [NW][2][16][VS]: weights of a row, high and low parts
+  const int tid = threadIdx.x, l = tid & 63, lr = l & 15, lg = l >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = a.nq / a.nkv, R = a.M * G, n_rb = (R + 16 * NW - 1) / (16 * NW);
+  // a KV head's row blocks run on one XCD (blocks b, b + 8, ...), whose L2
+  // then holds its pages; the longest first
+  const int jx = blockIdx.x >> 3;
+  const int kvh = (jx / n_rb) * 8 + (blockIdx.x & 7), rb = n_rb - 1 - jx % n_rb;
+  if (kvh >= a.nkv) return;
+  const int pos0 = *a.seq_len + a.pos_off, pmax = pos0 + a.M - 1;
+  const int r0 = rb * 16 * NW + 16 * w, rr = min(r0 + lr, R - 1);
+  const bool row_ok = r0 + lr < R;
+  const int m_row = rr / G, head = kvh * G + rr % G, row_pos = pos0 + m_row;
+  const int nc_row = row_pos / 64 + 1;                                                // pages of this lane's row,
+  const int nc_wave = r0 < R ? (pos0 + min(r0 + 15, R - 1) / G) / 64 + 1 : 0;         // of its wavefront's,
+  const int nc = (pos0 + min(rb * 16 * NW + 16 * NW - 1, R - 1) / G) / 64 + 1;        // of the block's
+  const int S = min(COMBINE_GROUPS, (a.max_chunks + 15) / 16);  // groups of the combine kernel
+  uint4 qh[KS], ql[KS];
+  {
+    const float scale = rsqrtf((float)HD);
+    const float* qp = a.q + (size_t)m_row * a.ldq + head * HD + lg * 8;
+#pragma unroll
+    for (int s2 = 0; s2 < KS; ++s2) {
+      const float4 u = *(const float4*)(qp + 32 * s2), v = *(const float4*)(qp + 32 * s2 + 4);
+      float x[8];
+      x[0] = row_ok ? u.x * scale : 0.f; x[1] = row_ok ? u.y * scale : 0.f;
+      x[2] = row_ok ? u.z * scale : 0.f; x[3] = row_ok ? u.w * scale : 0.f;
+      x[4] = row_ok ? v.x * scale : 0.f; x[5] = row_ok ? v.y * scale : 0.f;
+      x[6] = row_ok ? v.z * scale : 0.f; x[7] = row_ok ? v.w * scale : 0.f;
+      split8(x, qh[s2], ql[s2]);
+    }
+  }
+  const uint8_t* kc = (const uint8_t*)a.kcache;
+  const uint8_t* vc = (const uint8_t*)a.vcache;
+  // this thread's values: tokens 2 tp, 2 tp + 1 of dims 8 dg ..
+  const int tp = tid & 31, dg = tid >> 5;
+  const bool v_on = dg < HD / 8;
+  uint4 v0, v1;
+  auto fetch = [&](int j, int buf) {
+    const size_t base = (((size_t)a.layer * a.n_pages + a.block_table[j]) * a.nkv + kvh) * 64 * HD * 2;
+#pragma unroll
+    for (int i = 0; i < KT / NW; ++i) {
+      const int u = w * (KT / NW) + i, tg = u / KS, s2 = u % KS;
+      __builtin_amdgcn_global_load_lds((const void*)(kc + base + ((16 * tg + lr) * HD + 32 * s2 + 8 * lg) * 2),
+                                       (__attribute__((address_space(3))) void*)(kb + (buf * KT + u) * 1024), 16, 0, 0);
+    }
+    const uint8_t* vp = vc + base + (2 * tp * HD + 8 * (v_on ? dg : 0)) * 2;
+    v0 = ld16(vp);
+    v1 = ld16(vp + HD * 2);
+    // slots past the last row's position hold no value yet
+    const uint32_t m0 = j * 64 + 2 * tp <= pmax ? ~0u : 0u, m1 = j * 64 + 2 * tp + 1 <= pmax ? ~0u : 0u;
+    v0.x &= m0; v0.y &= m0; v0.z &= m0; v0.w &= m0;
+    v1.x &= m1; v1.y &= m1; v1.z &= m1; v1.w &= m1;
+  };
+  // the page after j in the combine's order (-1: none): runs of 16 pages,
+  // group sg taking runs sg, sg + S, ...
+  auto next = [&](int j) {
+    if ((j & 15) != 15 && j + 1 < nc) return j + 1;
+    const int run = j >> 4;
+    if ((run + S) * 16 < nc) return (run + S) * 16;
+    const int sg = run % S + 1;
+    return sg < S && sg * 16 < nc ? sg * 16 : -1;
+  };
+  float gm = -INFINITY, gl = 0.f, tm = -INFINITY, tl = 0.f;  // the group's running maximum and sum, and the total's
+  f32x4 ga[NT], ta[NT];
+#pragma unroll
+  for (int d = 0; d < NT; ++d) ga[d] = ta[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  uint32_t* ph_s = pb + (w * 2) * 16 * VS;
+  uint32_t* pl_s = ph_s + 16 * VS;
+  int buf = 0;
+  fetch(0, 0);
+  for (int j = 0; j >= 0; buf ^= 1) {
+    const int nj = next(j);
+    if (v_on) {
+      const uint32_t e0[4] = {v0.x, v0.y, v0.z, v0.w}, e1[4] = {v1.x, v1.y, v1.z, v1.w};
+      uint32_t* dst = vb + (buf * HD + 8 * dg) * VS + tp;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        dst[(2 * e) * VS] = (e0[e] & 0xFFFFu) | (e1[e] << 16);
+        dst[(2 * e + 1) * VS] = (e0[e] >> 16) | (e1[e] & 0xFFFF0000u);
+      }
+    }
+    // page j is in LDS, and page j - 1 no longer read
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (nj >= 0) fetch(nj, buf ^ 1);
+    if (j < nc_wave) {
+      // S^T tiles: lane holds tokens 16 tg + 4 lg + i of row lr
+      float pv[4][4], mx = -INFINITY;
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) {
+        f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s2 = 0; s2 < KS; ++s2) {
+          const uint4 kf = lds_ld16(kb + (buf * KT + tg * KS + s2) * 1024 + l * 16);
+          sc = mfma_tile<1>(kf, qh[s2], sc);
+          sc = mfma_tile<1>(kf, ql[s2], sc);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int t = j * 64 + 16 * tg + 4 * lg + i;
+          pv[tg][i] = (row_ok && t <= row_pos) ? sc[i] : -INFINITY;
+          mx = fmaxf(mx, pv[tg][i]);
+        }
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      float pl = 0.f;
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          pv[tg][i] = pv[tg][i] == -INFINITY ? 0.f : __expf(pv[tg][i] - mx);
+          sum += pv[tg][i];
+        }
+        sum += __shfl_xor(sum, 16);
+        sum += __shfl_xor(sum, 32);
+        pl = tg ? pl + sum : sum;
+        // the weights' high and low parts, for the lanes that need them
+        // as the operand of the next product
+        uint32_t hi[2], lo[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint16_t h0 = f32_to_bf16(pv[tg][2 * i]), h1 = f32_to_bf16(pv[tg][2 * i + 1]);
+          hi[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+          lo[i] = (uint32_t)f32_to_bf16(pv[tg][2 * i] - bf16_to_f32(h0)) |
+                  ((uint32_t)f32_to_bf16(pv[tg][2 * i + 1] - bf16_to_f32(h1)) << 16);
+        }
+        *(uint2*)&ph_s[lr * VS + 8 * tg + 2 * lg] = make_uint2(hi[0], hi[1]);
+        *(uint2*)&pl_s[lr * VS + 8 * tg + 2 * lg] = make_uint2(lo[0], lo[1]);
+      }
+      __builtin_amdgcn_wave_barrier();
+      uint4 ph[2], po[2];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        ph[ks] = *(const uint4*)&ph_s[lr * VS + 16 * ks + 4 * lg];
+        po[ks] = *(const uint4*)&pl_s[lr * VS + 16 * ks + 4 * lg];
+      }
+      __builtin_amdgcn_wave_barrier();
+      // fold: the scale of the running state and of this page
+      const float nm = fmaxf(gm, mx);
+      const float so = gm == -INFINITY ? 0.f : __expf(gm - nm), sn = __expf(mx - nm);
+      const bool in = j < nc_row;
+      gl = in ? fmaf(pl, sn, gl * so) : gl;
+      gm = in ? nm : gm;
+#pragma unroll
+      for (int d = 0; d < NT; ++d) {
+        f32x4 oc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          const uint4 vt = lds_ld16((const uint8_t*)&vb[(buf * HD + 16 * d + lr) * VS + 16 * ks + 4 * lg]);
+          oc = mfma_tile<1>(vt, ph[ks], oc);
+          oc = mfma_tile<1>(vt, po[ks], oc);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ga[d][i] = in ? fmaf(oc[i], sn, ga[d][i] * so) : ga[d][i];
+      }
+    }
+    const int sg = (j >> 4) % S;
+    if (nj < 0 || (nj >> 4) % S != sg) {  // the group ends: fold it into the total
+      const bool in = 16 * sg < nc_row;
+      const float nm = fmaxf(tm, gm);
+      const float so = tm == -INFINITY ? 0.f : __expf(tm - nm), sn = __expf(gm - nm);
+#pragma unroll
+      for (int d = 0; d < NT; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float f = fmaf(ga[d][i], sn, ta[d][i] * so);
+          ta[d][i] = sg == 0 ? ga[d][i] : in ? f : ta[d][i];
+          ga[d][i] = 0.f;
+        }
+      const float fl = fmaf(gl, sn, tl * so);
+      tl = sg == 0 ? gl : in ? fl : tl;
+      tm = sg == 0 ? gm : in ? nm : tm;
+      gm = -INFINITY;
+      gl = 0.f;
+    }
+    j = nj;
+  }
+  if (row_ok) {
+#pragma unroll
+    for (int d = 0; d < NT; ++d)
+      store4<1>((uint8_t*)a.out + tiled_row_off<1>(m_row, head * HD + 16 * d + 4 * lg, a.KT_tiled), 0,
+                make_float4(ta[d][0] / tl, ta[d][1] / tl, ta[d][2] / tl, ta[d][3] / tl));
+  }
+}
+
+hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s) {
+  const int rows = a.M * (a.nq / a.nkv), n_rb = (rows + 127) / 128;
+  const dim3 grid(8 * ((a.nkv + 7) / 8) * n_rb);
+  const int lds = 2 * (a.hd / 8) * 1024 + (2 * a.hd + 8 * 2 * 16) * 36 * 4;
+  const void* f = a.hd == 128 ? (const void*)k_attn_wide<128> : (const void*)k_attn_wide<64>;
+  hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  void* args[] = {(void*)&a};
+  return hipLaunchKernel(f, grid, dim3(512), args, lds, s);
 }
 
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {

@@ -140,6 +140,9 @@ struct DqnActArgs {
 // hipError_t of the launch.
 hipError_t launch_norm(int dtype, const NormArgs& a, hipStream_t s);
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s);
+// Any number of rows (bf16, tiled output): the bits of launch_attention's
+// matrix-core path.
+hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s);
 hipError_t launch_qnet_out(const QnetOutArgs& a, hipStream_t s);
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t s);
 hipError_t launch_sample(const SampleArgs& a, hipStream_t s);

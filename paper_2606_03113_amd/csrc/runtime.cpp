@@ -721,13 +721,21 @@ int run_wide(lede_ctx* c, int M, const int32_t* tokens, int pos_off, bool head, 
     qa.rope = c->S<float2>(o.rope);
     LAUNCH(LEDE_K_LINEAR_MFMA, bytes(qa), launch_wide(dt, qa, s));
 
-    for (int r = 0; r < M; r += MROWS) {
-      const int m = std::min(MROWS, M - r);
-      AttnArgs at = attn_args(c, j, m, false, pos_off + r);
-      at.q = c->S<float>(o.wq) + (size_t)r * o.qd;
-      at.out = c->S<uint8_t>(o.wattn) + (size_t)(r / 16) * KTq * TILE_BYTES; at.KT_tiled = KTq;
-      const double n_pos = (double)c->seq_len + pos_off + r + m;
-      LAUNCH(LEDE_K_ATTENTION, n_pos * o.kvd * 2.0 * o.es + 2.0 * m * o.qd * 4, launch_attention(dt, at, s));
+    if (dt == 1) {
+      AttnArgs at = attn_args(c, j, M, false, pos_off);
+      at.q = c->S<float>(o.wq);
+      at.out = c->S<uint8_t>(o.wattn); at.KT_tiled = KTq;
+      const double n_pos = (double)c->seq_len + pos_off + M;
+      LAUNCH(LEDE_K_ATTENTION, n_pos * o.kvd * 2.0 * o.es + 2.0 * M * o.qd * 4, launch_attention_wide(at, s));
+    } else {
+      for (int r = 0; r < M; r += MROWS) {
+        const int m = std::min(MROWS, M - r);
+        AttnArgs at = attn_args(c, j, m, false, pos_off + r);
+        at.q = c->S<float>(o.wq) + (size_t)r * o.qd;
+        at.out = c->S<uint8_t>(o.wattn) + (size_t)(r / 16) * KTq * TILE_BYTES; at.KT_tiled = KTq;
+        const double n_pos = (double)c->seq_len + pos_off + r + m;
+        LAUNCH(LEDE_K_ATTENTION, n_pos * o.kvd * 2.0 * o.es + 2.0 * m * o.qd * 4, launch_attention(dt, at, s));
+      }
     }
 
     WideArgs oa = base(lw.wo, o.d / 16, KTq, o.qd, EPI_RESID, c->S<void>(o.wattn));

@@ -48,8 +48,8 @@ def _check(model, max_ctx, ctx, n, piece=16):
     got = []
     for step in (n, piece):
         eng = _engine(model, max_ctx, ctx + n)
-        for i in range(0, ctx, 16):
-            eng.lede_prefill(toks[i:min(ctx, i + 16)])
+        for i in range(0, ctx, piece):
+            eng.lede_prefill(toks[i:min(ctx, i + piece)])
         for i in range(ctx, ctx + n, step):
             eng.lede_prefill(toks[i:min(ctx + n, i + step)])
         got.append(_state(eng))
@@ -72,6 +72,12 @@ def test_prefill_of_several_passes(model):
     """More rows than one pass takes, ending in a ragged pass."""
     say("wide prefill, several passes", model.name)
     _check(model, 2400, 40, 2201)
+
+
+def test_prefill_past_128_pages():
+    """Contexts longer than one round of the page combine's eight groups."""
+    say("wide prefill, 130 pages")
+    _check(shrink(GQA_64, n_layers=1, exits=(1,)), 8400, 8190, 130)
 
 
 @pytest.mark.parametrize("n", [40, 200])
