@@ -14,32 +14,55 @@ namespace lede {
 
 // ---- y = W x -----------------------------------------------------------------
 
-// What a kernel does with a finished 16 x 16 output tile: lane (lr, lg) holds
-// columns 4 lg + i of weight group g and row m.  Called by whole wavefronts.
+// The operands of a finished 16 x 16 output tile's epilogue, loaded for all of
+// a wavefront's tiles before the first is finished: a load behind another
+// tile's store would wait for a round trip each.
+template <int EPI> struct Extra {  // EPI_RESID: the residual and the next norm's gains
+  float4 x, y;                     // EPI_QKV: the rotary pairs
+  int page;                        // EPI_QKV: the row's cache page (keys and values)
+  float inv;                       // the row's scale
+};
+
+// Lane (lr, lg) holds columns 4 lg + i of weight group g and row m.  Tiles past
+// the matrix load some in-range operand.
 template <int DT, int EPI>
-__device__ __forceinline__ void finish(const WideArgs& a, int g, int m, float (&v)[4]) {
+__device__ __forceinline__ void finish_load(const WideArgs& a, int g, int m, Extra<EPI>& e) {
+  const int lg = (threadIdx.x & 63) >> 4;
+  const int mr = min(m, a.M - 1), gc = min(g, a.n_groups - 1);
+  e.inv = a.inv ? a.inv[mr] : 1.f;
+  if (EPI == EPI_RESID) {
+    const int col = gc * 16 + 4 * lg;
+    e.x = *(const float4*)(a.h + (size_t)mr * a.ldh + col);
+    e.y = a.ss_out ? row_load4<DT>(nullptr, a.xg_gain, col) : make_float4(0.f, 0.f, 0.f, 0.f);
+  } else if (EPI == EPI_QKV) {
+    const int gph = a.hd / 16, qg = a.nq * gph, kg = a.nkv * gph;
+    const int pos = *a.seq_len + a.pos_off + mr;
+    e.page = gc >= qg ? a.block_table[pos >> 6] : 0;
+    const int gl = gc < qg ? gc : gc < qg + kg ? gc - qg : 0;
+    const float2* rp = a.rope + (size_t)pos * (a.hd / 2) + 8 * (gl % gph) + 4 * (lg & 1);
+    e.x = *(const float4*)rp;
+    e.y = *(const float4*)(rp + 2);
+  }
+}
+
+// Called by whole wavefronts.
+template <int DT, int EPI>
+__device__ __forceinline__ void finish(const WideArgs& a, int g, int m, float (&v)[4], const Extra<EPI>& e) {
   typedef Tile<DT> TL;
   const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
   const bool row = m < a.M;
-  const int mr = row ? m : 0;
   if (a.inv) {
-    const float s = a.inv[mr];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] *= s;
+    for (int i = 0; i < 4; ++i) v[i] *= e.inv;
   }
   if (EPI == EPI_RESID) {
     const int col = g * 16 + 4 * lg;
-    float* hp = a.h + (size_t)mr * a.ldh + col;
-    float gn[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) gn[i] = a.ss_out ? Elem<DT>::load(a.xg_gain, col + i) : 0.f;
-    const float4 h4 = *(const float4*)hp;
-    v[0] = h4.x + v[0]; v[1] = h4.y + v[1]; v[2] = h4.z + v[2]; v[3] = h4.w + v[3];
-    if (row) *(float4*)hp = make_float4(v[0], v[1], v[2], v[3]);
+    v[0] = e.x.x + v[0]; v[1] = e.x.y + v[1]; v[2] = e.x.z + v[2]; v[3] = e.x.w + v[3];
+    if (row) *(float4*)(a.h + (size_t)m * a.ldh + col) = make_float4(v[0], v[1], v[2], v[3]);
     if (a.ss_out) {
       if (row)
         store4<DT>((uint8_t*)a.xg + tiled_row_off<DT>(m, col, a.KT_out), 0,
-                   make_float4(v[0] * gn[0], v[1] * gn[1], v[2] * gn[2], v[3] * gn[3]));
+                   make_float4(v[0] * e.y.x, v[1] * e.y.y, v[2] * e.y.z, v[3] * e.y.w));
       // the group's sum of squares in column order: the running sum passes
       // through the four lanes of a row
       float s = 0.f;
@@ -66,36 +89,36 @@ __device__ __forceinline__ void finish(const WideArgs& a, int g, int m, float (&
   } else {
     const int hd = a.hd, gph = hd / 16;
     const int qg = a.nq * gph, kg = a.nkv * gph;
-    const int pos = *a.seq_len + a.pos_off + mr;
-    if (g < qg + kg) {
-      const bool isq = g < qg;
+    const int pos = *a.seq_len + a.pos_off + m;
+    const bool isq = g < qg, rot = g < qg + kg;
+    float y[4];
+    int head, dim;
+    if (rot) {
       const int gl = isq ? g : g - qg;
-      const int head = gl / gph, i0 = 8 * (gl % gph) + 4 * (lg & 1);
-      const float2* rp = a.rope + (size_t)pos * (hd / 2) + i0;
-      float y[4];
+      const float2 cs[4] = {make_float2(e.x.x, e.x.y), make_float2(e.x.z, e.x.w), make_float2(e.y.x, e.y.y),
+                            make_float2(e.y.z, e.y.w)};
+      head = gl / gph;
+      dim = 8 * (gl % gph) + 4 * (lg & 1) + (lg < 2 ? 0 : hd / 2);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float2 cs = rp[i];
         const float other = __shfl_xor(v[i], 32);
-        const float x0 = lg < 2 ? v[i] : other, x1 = lg < 2 ? other : v[i];
-        const float2 yy = rope_pair(x0, x1, cs);
+        const float2 yy = rope_pair(lg < 2 ? v[i] : other, lg < 2 ? other : v[i], cs[i]);
         y[i] = lg < 2 ? yy.x : yy.y;
       }
-      const int dim = i0 + (lg < 2 ? 0 : hd / 2);
-      if (row) {
-        if (isq) {
-          *(float4*)(a.q + (size_t)m * a.ldq + head * hd + dim) = make_float4(y[0], y[1], y[2], y[3]);
-        } else {
-          const size_t base =
-              ((((size_t)a.layer * a.n_pages + a.block_table[pos >> 6]) * a.nkv + head) * 64 + (pos & 63)) * hd + dim;
-          store4<DT>((uint8_t*)a.kcache + base * TL::ES, 0, make_float4(y[0], y[1], y[2], y[3]));
-        }
+    } else {
+      head = (g - qg - kg) / gph;
+      dim = 16 * ((g - qg - kg) % gph) + 4 * lg;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[i] = v[i];
+    }
+    if (row) {
+      const float4 y4 = make_float4(y[0], y[1], y[2], y[3]);
+      if (isq) {
+        *(float4*)(a.q + (size_t)m * a.ldq + head * hd + dim) = y4;
+      } else {
+        const size_t at = ((((size_t)a.layer * a.n_pages + e.page) * a.nkv + head) * 64 + (pos & 63)) * hd + dim;
+        store4<DT>((uint8_t*)(rot ? a.kcache : a.vcache) + at * TL::ES, 0, y4);
       }
-    } else if (row) {
-      const int dim = (g - qg - kg) * 16 + 4 * lg;
-      const size_t base =
-          ((((size_t)a.layer * a.n_pages + a.block_table[pos >> 6]) * a.nkv + dim / hd) * 64 + (pos & 63)) * hd + dim % hd;
-      store4<DT>((uint8_t*)a.vcache + base * TL::ES, 0, make_float4(v[0], v[1], v[2], v[3]));
     }
   }
 }
@@ -174,6 +197,14 @@ __global__ __launch_bounds__(512) void k_wide(WideArgs a) {
     }
   }
 
+  // the output tiles this wavefront finishes, wave, wave + 8, ...
+  constexpr int FT = (TN * TM + NW - 1) / NW;
+  Extra<EPI> e[FT];
+#pragma unroll
+  for (int f = 0; f < FT; ++f) {
+    const int tt = min(wave + NW * f, TN * TM - 1);
+    finish_load<DT, EPI>(a, g0 + tt / TM, (r0 + tt % TM) * 16 + lr, e[f]);
+  }
   float4* part = (float4*)smem;  // [NW][TN * TM][64]
 #pragma unroll
   for (int i = 0; i < TN; ++i)
@@ -184,38 +215,44 @@ __global__ __launch_bounds__(512) void k_wide(WideArgs a) {
     }
   __syncthreads();
 
-  // output tiles wave, wave + 8, ...: lane holds columns 4 lg + i of row lr
-  for (int tt = wave; tt < TN * TM; tt += NW) {
-    const int g = g0 + tt / TM, m = (r0 + tt % TM) * 16 + lr;
-    if (g >= a.n_groups || (r0 + tt % TM) * 16 >= a.M) continue;  // uniform
-    float4 v4 = part[tt * 64 + lane];
+#pragma unroll
+  for (int f = 0; f < FT; ++f) {
+    const int tt = wave + NW * f, g = g0 + tt / TM, rg = r0 + tt % TM;
+    if (tt >= TN * TM || g >= a.n_groups || rg >= MG) continue;  // uniform
+    const float4 v4 = part[tt * 64 + lane];
     float v[4] = {v4.x, v4.y, v4.z, v4.w};
 #pragma unroll
     for (int q = 1; q < NW; ++q) {
       const float4 p = part[(q * TN * TM + tt) * 64 + lane];
       v[0] += p.x; v[1] += p.y; v[2] += p.z; v[3] += p.w;
     }
-    finish<DT, EPI>(a, g, m, v);
+    finish<DT, EPI>(a, g, rg * 16 + lr, v, e[f]);
   }
 }
 
 // Both operands staged in LDS for WN x WM wavefronts of TN x TM tiles each:
 // a block computes (WN TN 16) x (WM TM 16) outputs.  The K tiles are walked in
-// the order the sum above asks for: class (w, 0) = tiles w, w + 16, ..., then
-// (w, 1) = w + 8, w + 24, ..., w = 0..7; c accumulates a class, c0 keeps the
-// even one, s the sum so far.  A stage is one K tile of every row group of the
-// block (direct global-to-LDS copies of whole 1 KiB tiles, which are in
-// operand order, so the reads have no bank conflicts); S stages are in flight.
+// the order the sum above asks for: class w = tiles w, w + 16, ... into one
+// accumulator, class w + 8 into another, their sum onto the total, w = 0..7.
+// The ring in LDS holds S K tiles of every row group of the block (direct
+// global-to-LDS copies of whole 1 KiB tiles, which are in operand order, so the
+// reads have no bank conflicts).  While a K tile is multiplied, the next one's
+// operands are read into registers (all of them, or where three sets of
+// accumulators leave no room PF of the TN weight tiles) and later ones are
+// copied.  What is left over the products' time is the barrier per K tile
+// (70 ns of 410 for 256 x 128 outputs), the copies (70 ns) and 14 us a launch.
 template <int N>
 __device__ __forceinline__ void stage_barrier() {  // this wavefront's copies but the last N, and its LDS reads; then all
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-template <int DT, int TN, int TM, int WN, int WM, int S, int EPI>
+template <int DT, int TN, int TM, int WN, int WM, int S, int PF, int EPI>
 __global__ __launch_bounds__(WN * WM * 64, 2) void k_wide_lds(WideArgs a) {
   constexpr int NWV = WN * WM, GN = WN * TN, GM = WM * TM, TILES = GN + GM;
-  static_assert(TILES % NWV == 0, "every wavefront copies the same number of tiles");
-  constexpr int PER = TILES / NWV;
+  constexpr int D = PF == TN ? S : S - 1;  // copies run this many tiles ahead
+  // every wavefront copies the same number of tiles (the last ones some twice),
+  // so that one count of outstanding copies holds for all
+  constexpr int PER = (TILES + NWV - 1) / NWV;
   extern __shared__ __align__(16) uint8_t smem[];  // [S][TILES][1 KiB]
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -225,7 +262,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_wide_lds(WideArgs a) {
   const uint8_t* src[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int u = wave * PER + i;
+    const int u = min(wave * PER + i, TILES - 1);
     src[i] = (u < GN ? a.w + (size_t)min(g0 + u, a.n_groups - 1) * KT * TILE_BYTES
                      : a.x + (size_t)min(r0 + u - GN, MG - 1) * KT * TILE_BYTES) + lane * 16;
   }
@@ -242,58 +279,84 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_wide_lds(WideArgs a) {
 #pragma unroll
     for (int i = 0; i < PER; ++i)
       __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)t * TILE_BYTES),
-                                       (__attribute__((address_space(3))) void*)(smem + (slot * TILES + wave * PER + i) * TILE_BYTES),
+                                       (__attribute__((address_space(3))) void*)(smem + (slot * TILES + min(wave * PER + i, TILES - 1)) * TILE_BYTES),
                                        16, 0, 0);
   };
-  int lt = 0, lbase = 0;  // the walk of the copies, S - 1 tiles ahead
-  for (int i = 0; i < S - 1; ++i)
+  int lt = 0, lbase = 0;  // the walk of the copies, D tiles ahead
+  for (int i = 0; i < D; ++i)
     if (i < KT) {
       stage(i, lt);
       next(lt, lbase);
     }
-  f32x4 c[TN][TM], c0[TN][TM], s[TN][TM];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int k = 0; k < TM; ++k) c[i][k] = c0[i][k] = s[i][k] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int wn = wave % WN, wm = wave / WN;
   const uint32_t la = wn * TN * TILE_BYTES + lane * 16, lb = (GN + wm * TM) * TILE_BYTES + lane * 16;
-  int t = 0, base = 0, slot = 0;
-  for (int st = 0; st < KT; ++st) {
-    if (st + S - 1 <= KT) stage_barrier<(S - 2) * PER>();
-    else stage_barrier<0>();
-    if (st + S - 1 < KT) {
-      stage(slot == 0 ? S - 1 : slot - 1, lt);
-      next(lt, lbase);
-    }
+  // the operands of the next K tile (of the weights, PF tiles), and the rest
+  uint4 wnext[PF], xnext[TM];
+  auto read = [&](int slot) {
     const uint32_t o = slot * TILES * TILE_BYTES;
+#pragma unroll
+    for (int i = 0; i < PF; ++i) wnext[i] = lds_ld16(smem + (o + la + i * TILE_BYTES));
+#pragma unroll
+    for (int i = 0; i < TM; ++i) xnext[i] = lds_ld16(smem + (o + lb + i * TILE_BYTES));
+  };
+  int st = 0, slot = 0;
+  // one K tile, whose operands have been read: a later tile's copy is started
+  // and the next one's operands are read before the products
+  auto step = [&](f32x4 (&c)[TN][TM], bool first) {
+    if (st + D <= KT) stage_barrier<(D - 2) * PER>();
+    else stage_barrier<0>();
     uint4 wv[TN], xv[TM];
 #pragma unroll
-    for (int i = 0; i < TN; ++i) wv[i] = lds_ld16(smem + (o + la + i * TILE_BYTES));
+    for (int i = 0; i < TN; ++i) wv[i] = i < PF ? wnext[i < PF ? i : 0] : lds_ld16(smem + (slot * TILES * TILE_BYTES + la + i * TILE_BYTES));
 #pragma unroll
-    for (int i = 0; i < TM; ++i) xv[i] = lds_ld16(smem + (o + lb + i * TILE_BYTES));
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int k = 0; k < TM; ++k) c[i][k] = mfma_tile<DT>(wv[i], xv[k], c[i][k]);
+    for (int i = 0; i < TM; ++i) xv[i] = xnext[i];
+    if (st + D < KT) {
+      stage(PF == TN ? slot : slot == 0 ? S - 1 : slot - 1, lt);
+      next(lt, lbase);
+    }
     slot = slot == S - 1 ? 0 : slot + 1;
-    if (t + 16 >= KT) {  // the class ends
-      const bool odd = base >= 8;
+    read(slot);
+    ++st;
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+#pragma unroll
+      for (int k = 0; k < TM; ++k) c[i][k] = mfma_tile<DT>(wv[i], xv[k], first ? f32x4{0.f, 0.f, 0.f, 0.f} : c[i][k]);
+      if (i == PF - 1) __builtin_amdgcn_sched_barrier(0);  // the products whose operands are here come first
+    }
+  };
+  auto sum_class = [&](f32x4 (&c)[TN][TM], int base) {
+    if (base < KT) {
+      step(c, true);
+      for (int t = base + 16; t < KT; t += 16) step(c, false);
+    } else {
 #pragma unroll
       for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int k = 0; k < TM; ++k) {
-          if (odd || KT - base <= 8) {  // (no tile w + 8 when K is that short)
-            s[i][k] += c0[i][k] + c[i][k];
-            c0[i][k] = f32x4{0.f, 0.f, 0.f, 0.f};
-          } else {
-            c0[i][k] = c[i][k];
-          }
-          c[i][k] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int k = 0; k < TM; ++k) c[i][k] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    next(t, base);
+  };
+  if (KT >= D) stage_barrier<(D - 1) * PER>();
+  else stage_barrier<0>();
+  read(0);
+  f32x4 s[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int k = 0; k < TM; ++k) s[i][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int w = 0; w < LIN_WAVES; ++w) {
+    f32x4 c0[TN][TM], c1[TN][TM];
+    sum_class(c0, w);
+    sum_class(c1, w + LIN_WAVES);
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int k = 0; k < TM; ++k) s[i][k] += c0[i][k] + c1[i][k];
   }
+  Extra<EPI> e[TN][TM];
+#pragma unroll
+  for (int k = 0; k < TM; ++k)
+#pragma unroll
+    for (int i = 0; i < TN; ++i) finish_load<DT, EPI>(a, g0 + wn * TN + i, (r0 + wm * TM + k) * 16 + lr, e[i][k]);
 #pragma unroll
   for (int k = 0; k < TM; ++k)
 #pragma unroll
@@ -301,7 +364,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_wide_lds(WideArgs a) {
       const int g = g0 + wn * TN + i, rg = r0 + wm * TM + k;
       if (g < a.n_groups && rg < MG) {
         float v[4] = {s[i][k][0], s[i][k][1], s[i][k][2], s[i][k][3]};
-        finish<DT, EPI>(a, g, rg * 16 + lr, v);
+        finish<DT, EPI>(a, g, rg * 16 + lr, v, e[i][k]);
       }
     }
 }
@@ -361,43 +424,45 @@ static hipError_t launch_shape(WideArgs& a, hipStream_t s) {
   return launch_tiles(f, a, TN, TM, LIN_WAVES * 64, (size_t)LIN_WAVES * TN * TM * 1024, s);
 }
 
-template <int DT, int TN, int TM, int WN, int WM, int S>
+template <int DT, int TN, int TM, int WN, int WM, int S, int PF>
 static hipError_t launch_staged(WideArgs& a, hipStream_t s) {
-  const void* f = a.epi == EPI_QKV     ? (const void*)k_wide_lds<DT, TN, TM, WN, WM, S, EPI_QKV>
-                  : a.epi == EPI_RESID ? (const void*)k_wide_lds<DT, TN, TM, WN, WM, S, EPI_RESID>
-                                       : (const void*)k_wide_lds<DT, TN, TM, WN, WM, S, EPI_SWIGLU>;
+  const void* f = a.epi == EPI_QKV     ? (const void*)k_wide_lds<DT, TN, TM, WN, WM, S, PF, EPI_QKV>
+                  : a.epi == EPI_RESID ? (const void*)k_wide_lds<DT, TN, TM, WN, WM, S, PF, EPI_RESID>
+                                       : (const void*)k_wide_lds<DT, TN, TM, WN, WM, S, PF, EPI_SWIGLU>;
   return launch_tiles(f, a, WN * TN, WM * TM, WN * WM * 64, (size_t)S * (WN * TN + WM * TM) * TILE_BYTES, s);
 }
 
 // Which kernel: the one with the least estimated time on 256 CUs, from the tile
-// area per block and each kernel's rate when every CU is busy, measured on the
-// Llama-2-7B layer at 2048 rows: 256 x 128 staged tiles 755 TFLOP/s, 128 x 128
-// 640, 128 x 64 (two blocks per CU) 625, and 470 for the 32 x 64 tiles of
-// k_wide.  Smaller tiles win where larger ones leave CUs idle: at 512 rows
-// 128 x 64 takes 429 us a layer against 544 for 256 x 128 and 526 for 32 x 64,
-// at 128 rows 283, 463 and 203.  A lone block of a kernel made for two per CU
-// runs at about 0.65 of the CU's rate.
+// area per block and each kernel's rate when every CU is busy (TFLOP/s measured
+// at 2048 rows of the Llama-2-13B widths, 512 rows for the smaller tiles; two
+// blocks of any of them fit a CU).  A lone block on a CU runs at about 0.65 of
+// the CU's rate.  Smaller tiles win where larger ones leave CUs idle: at 512
+// rows, N = K = 4096, 64 x 64 tiles take 36 us against 40 for 128 x 64, 46 for
+// 96 x 128, 49 for 128 x 128 and 39 for the 32 x 64 tiles of k_wide; at
+// N = 22016, 188, 131, 114, 119 and 190; at 97 rows, N = 28672, 65, 47, 53, 49
+// and 61.  The fp32 models are small: they take two of the shapes.
 template <int DT>
 static hipError_t launch_dt(WideArgs& a, hipStream_t s) {
-  struct Shape { int n, m, resident; double rate; };
-  static const Shape shapes[4] = {{32, 64, 2, 470.}, {128, 64, 2, 625.}, {128, 128, 1, 640.}, {256, 128, 1, 755.}};
+  struct Shape { int n, m; double rate; };
+  static const Shape shapes[5] = {{32, 64, 470.}, {128, 64, 720.}, {64, 64, 560.}, {96, 128, 840.}, {128, 128, 900.}};
   int best = 0;
   double best_t = 0.;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < (DT == 1 ? 5 : 2); ++i) {
     const Shape& p = shapes[i];
     const int blocks = ((a.n_groups * 16 + p.n - 1) / p.n) * ((a.M + p.m - 1) / p.m), load = (blocks + 255) / 256;
-    const double t = load * p.n * p.m / (p.rate * (load < p.resident ? 0.65 : 1.));
+    const double t = load * p.n * p.m / (p.rate * (load < 2 ? 0.65 : 1.));
     if (i == 0 || t < best_t) {
       best = i;
       best_t = t;
     }
   }
-  switch (best) {
-    case 0: return launch_shape<DT, 2, 4, 2>(a, s);
-    case 1: return launch_staged<DT, 4, 2, 2, 2, 5>(a, s);
-    case 2: return launch_staged<DT, 4, 2, 2, 4, 6>(a, s);
-    default: return launch_staged<DT, 4, 4, 4, 2, 6>(a, s);
+  if (best == 0) return launch_shape<DT, 2, 4, 2>(a, s);
+  if (best == 1) return launch_staged<DT, 4, 2, 2, 2, 5, 4>(a, s);
+  if (DT == 1) {
+    if (best == 2) return launch_staged<1, 2, 2, 2, 2, 8, 2>(a, s);
+    if (best == 3) return launch_staged<1, 3, 4, 2, 2, 5, 3>(a, s);
   }
+  return launch_staged<1, 4, 4, 2, 2, 5, 1>(a, s);
 }
 
 hipError_t launch_wide(int dtype, WideArgs a, hipStream_t s) { return dtype == 1 ? launch_dt<1>(a, s) : launch_dt<0>(a, s); }
