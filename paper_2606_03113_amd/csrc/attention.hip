@@ -216,10 +216,8 @@ __device__ __forceinline__ void split8(const float* x, uint4& hi, uint4& lo) {
   uint32_t h[4], l[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const uint16_t h0 = f32_to_bf16(x[2 * i]), h1 = f32_to_bf16(x[2 * i + 1]);
-    const uint16_t l0 = f32_to_bf16(x[2 * i] - bf16_to_f32(h0)), l1 = f32_to_bf16(x[2 * i + 1] - bf16_to_f32(h1));
-    h[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-    l[i] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+    h[i] = f32_to_bf16x2(x[2 * i], x[2 * i + 1]);
+    l[i] = f32_to_bf16x2(x[2 * i] - bf16lo(h[i]), x[2 * i + 1] - bf16hi(h[i]));
   }
   hi = make_uint4(h[0], h[1], h[2], h[3]);
   lo = make_uint4(l[0], l[1], l[2], l[3]);
@@ -393,6 +391,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   }
 }
 
+// The sum (or maximum) of the values of lanes l and l ^ X, X = 16 or 32, as
+// vector instructions: a lane swap leaves the value of the lane without bit X
+// in r[0] of both and that of the lane with it in r[1].
+template <int X, bool MAX>
+__device__ __forceinline__ float pair_lanes(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto r = X == 32 ? __builtin_amdgcn_permlane32_swap(u, u, false, false) : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+  return MAX ? fmaxf(a, b) : a + b;
+}
+
 // Attention of a prefill pass's rows (bf16 cache): 8 wavefronts of 16 query
 // rows walk a KV head's pages together, each page staged in LDS once for all
 // of them -- keys as matrix-core tiles (direct global-to-LDS copies), values
@@ -427,6 +436,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   const int m_row = rr / G, head = kvh * G + rr % G, row_pos = pos0 + m_row;
   const int nc_row = row_pos / 64 + 1;                                                // pages of this lane's row,
   const int nc_wave = r0 < R ? (pos0 + min(r0 + 15, R - 1) / G) / 64 + 1 : 0;         // of its wavefront's,
+  const int nc_full = (pos0 + min(r0, R - 1) / G + 1) / 64;                            // those its first row sees whole,
   const int nc = (pos0 + min(rb * 16 * NW + 16 * NW - 1, R - 1) / G) / 64 + 1;        // of the block's
   const int S = min(COMBINE_GROUPS, (a.max_chunks + 15) / 16);  // groups of the combine kernel
   uint4 qh[KS], ql[KS];
@@ -461,10 +471,6 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
     const uint8_t* vp = vc + base + (2 * tp * HD + 8 * (v_on ? dg : 0)) * 2;
     v0 = ld16(vp);
     v1 = ld16(vp + HD * 2);
-    // slots past the last row's position hold no value yet
-    const uint32_t m0 = j * 64 + 2 * tp <= pmax ? ~0u : 0u, m1 = j * 64 + 2 * tp + 1 <= pmax ? ~0u : 0u;
-    v0.x &= m0; v0.y &= m0; v0.z &= m0; v0.w &= m0;
-    v1.x &= m1; v1.y &= m1; v1.z &= m1; v1.w &= m1;
   };
   // the page after j in the combine's order (-1: none): runs of 16 pages,
   // group sg taking runs sg, sg + S, ...
@@ -488,16 +494,19 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
     if (v_on) {
       const uint32_t e0[4] = {v0.x, v0.y, v0.z, v0.w}, e1[4] = {v1.x, v1.y, v1.z, v1.w};
       uint32_t* dst = vb + (buf * HD + 8 * dg) * VS + tp;
+      // slots past the last row's position hold no value yet
+      const uint32_t vm = (j * 64 + 2 * tp <= pmax ? 0xFFFFu : 0u) | (j * 64 + 2 * tp + 1 <= pmax ? 0xFFFF0000u : 0u);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        dst[(2 * e) * VS] = (e0[e] & 0xFFFFu) | (e1[e] << 16);
-        dst[(2 * e + 1) * VS] = (e0[e] >> 16) | (e1[e] & 0xFFFF0000u);
+        dst[(2 * e) * VS] = __builtin_amdgcn_perm(e1[e], e0[e], 0x05040100u) & vm;
+        dst[(2 * e + 1) * VS] = __builtin_amdgcn_perm(e1[e], e0[e], 0x07060302u) & vm;
       }
     }
     // page j is in LDS, and page j - 1 no longer read
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (nj >= 0) fetch(nj, buf ^ 1);
     if (j < nc_wave) {
+      const bool ends = j >= nc_full;  // some row of the wavefront ends in or before this page
       // S^T tiles: lane holds tokens 16 tg + 4 lg + i of row lr
       float pv[4][4], mx = -INFINITY;
 #pragma unroll
@@ -512,33 +521,34 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int t = j * 64 + 16 * tg + 4 * lg + i;
-          pv[tg][i] = (row_ok && t <= row_pos) ? sc[i] : -INFINITY;
+          pv[tg][i] = sc[i];
+          if (ends && t > row_pos) pv[tg][i] = -INFINITY;
           mx = fmaxf(mx, pv[tg][i]);
         }
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      mx = pair_lanes<32, true>(pair_lanes<16, true>(mx));
+      // a row that ends before this page takes no part in it: weights of 0,
+      // folded with factors that leave its state as it is
+      const bool in = j < nc_row;
+      const float ms = in ? mx : 0.f;
       float pl = 0.f;
 #pragma unroll
       for (int tg = 0; tg < 4; ++tg) {
         float sum = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          pv[tg][i] = pv[tg][i] == -INFINITY ? 0.f : __expf(pv[tg][i] - mx);
+          pv[tg][i] = __expf(pv[tg][i] - ms);  // 0 where masked
           sum += pv[tg][i];
         }
-        sum += __shfl_xor(sum, 16);
-        sum += __shfl_xor(sum, 32);
+        sum = pair_lanes<32, false>(pair_lanes<16, false>(sum));
         pl = tg ? pl + sum : sum;
         // the weights' high and low parts, for the lanes that need them
         // as the operand of the next product
         uint32_t hi[2], lo[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const uint16_t h0 = f32_to_bf16(pv[tg][2 * i]), h1 = f32_to_bf16(pv[tg][2 * i + 1]);
-          hi[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-          lo[i] = (uint32_t)f32_to_bf16(pv[tg][2 * i] - bf16_to_f32(h0)) |
-                  ((uint32_t)f32_to_bf16(pv[tg][2 * i + 1] - bf16_to_f32(h1)) << 16);
+          hi[i] = f32_to_bf16x2(pv[tg][2 * i], pv[tg][2 * i + 1]);
+          lo[i] = f32_to_bf16x2(pv[tg][2 * i] - bf16lo(hi[i]), pv[tg][2 * i + 1] - bf16hi(hi[i]));
         }
         *(uint2*)&ph_s[lr * VS + 8 * tg + 2 * lg] = make_uint2(hi[0], hi[1]);
         *(uint2*)&pl_s[lr * VS + 8 * tg + 2 * lg] = make_uint2(lo[0], lo[1]);
@@ -552,11 +562,10 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
       }
       __builtin_amdgcn_wave_barrier();
       // fold: the scale of the running state and of this page
-      const float nm = fmaxf(gm, mx);
-      const float so = gm == -INFINITY ? 0.f : __expf(gm - nm), sn = __expf(mx - nm);
-      const bool in = j < nc_row;
-      gl = in ? fmaf(pl, sn, gl * so) : gl;
-      gm = in ? nm : gm;
+      const float nm = in ? fmaxf(gm, mx) : gm;
+      const float so = !in ? 1.f : gm == -INFINITY ? 0.f : __expf(gm - nm), sn = in ? __expf(mx - nm) : 0.f;
+      gl = fmaf(pl, sn, gl * so);
+      gm = nm;
 #pragma unroll
       for (int d = 0; d < NT; ++d) {
         f32x4 oc = {0.f, 0.f, 0.f, 0.f};
@@ -567,7 +576,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
           oc = mfma_tile<1>(vt, po[ks], oc);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) ga[d][i] = in ? fmaf(oc[i], sn, ga[d][i] * so) : ga[d][i];
+        for (int i = 0; i < 4; ++i) ga[d][i] = fmaf(oc[i], sn, ga[d][i] * so);
       }
     }
     const int sg = (j >> 4) % S;

@@ -18,11 +18,13 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// Round fp32 to bf16, nearest-even (finite inputs).
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// Round fp32 to bf16, nearest-even: the conversion instruction (the same bits
+// as adding 0x7FFF plus the kept part's lowest bit, checked for every fp32
+// value that is not a NaN), alone and for a pair packed low half first.
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ uint32_t f32_to_bf16x2(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
 template <int DT> struct Elem;
@@ -133,9 +135,7 @@ __device__ __forceinline__ float4 row_load4(const float* h, const void* row, int
 template <int DT>
 __device__ __forceinline__ void store4(uint8_t* base, int i, float4 y) {
   if (DT == 1) {
-    const uint32_t lo = (uint32_t)f32_to_bf16(y.x) | ((uint32_t)f32_to_bf16(y.y) << 16);
-    const uint32_t hi = (uint32_t)f32_to_bf16(y.z) | ((uint32_t)f32_to_bf16(y.w) << 16);
-    *(uint2*)(base + (size_t)i * 2) = make_uint2(lo, hi);
+    *(uint2*)(base + (size_t)i * 2) = make_uint2(f32_to_bf16x2(y.x, y.y), f32_to_bf16x2(y.z, y.w));
   } else {
     *(float4*)(base + (size_t)i * 4) = y;
   }
