@@ -52,20 +52,24 @@ __global__ void k_accept(AcceptArgs a) {
 __global__ __launch_bounds__(SB) void k_sample(SampleArgs a) {
   __shared__ float red[SW];
   __shared__ int ired[SW];
-  const float u = a.u ? a.u[a.u_index] : a.u_imm;
+  const int row = blockIdx.x;
+  const float u = a.u ? a.u[a.u_index] : a.u_imm[row];
   const float it = a.inv_t;
+  const float* z = a.logits + (size_t)row * a.ld;
   float2 st;
   int tok;
   if (a.gstats) {  // from the head's group statistics: no pass over the row
-    st = group_row_stats(a.gstats, a.n_groups, it, red);
-    tok = group_draw(a.gstats, a.logits, a.n_groups, st.x, it, u, red, ired);
+    const GroupChunk ch(a.gstats, a.n_groups);
+    st.x = block_max_f(ch.max(), red);
+    tok = draw_group(ch, ch.sum(st.x, it), z, st.x, it, u, st.y, red, ired);
   } else {
-    st = row_stats(a.logits, a.vocab, it, red);
+    float s;
+    st.x = row_max_sum(z, a.vocab, it, s, red);
     const float m = st.x;
-    tok = block_draw([&](float x, float) { return expf((x - m) * it); }, a.logits, nullptr, a.vocab, u, red, ired);
+    tok = draw_chunk([&](float x, float) { return expf((x - m) * it); }, s, z, nullptr, a.vocab, u, st.y, red, ired);
   }
   if (threadIdx.x == 0) {
-    key_store_token(a.key_out, 0, tok);
+    key_store_token(a.key_out, row, tok);
     if (a.stats_out) {
       a.stats_out[0] = st.x;
       a.stats_out[1] = st.y;
@@ -73,23 +77,30 @@ __global__ __launch_bounds__(SB) void k_sample(SampleArgs a) {
   }
 }
 
+// (max, sum of exp((z - max) * inv_t)) of the rows, one block each.
+__global__ __launch_bounds__(SB) void k_row_stats(RowStatsArgs a) {
+  __shared__ float red[SW];
+  const int row = blockIdx.x;
+  if (a.record && row > a.record[0]) return;  // rows past the accepted ones and the bonus row
+  const float2 st = a.gstats ? group_row_stats(a.gstats + (size_t)row * a.n_groups, a.n_groups, a.inv_t, red)
+                             : row_stats(a.logits + (size_t)row * a.ld, a.vocab, a.inv_t, red);
+  if (threadIdx.x == 0) {
+    a.out[2 * row] = st.x;
+    a.out[2 * row + 1] = st.y;
+  }
+}
+
 // Speculative-sampling acceptance of the k drafts, the draw of the token
-// after them, and the commit.
+// after them, and the commit, from the rows' statistics (k_row_stats: the rows
+// side by side; one block that took them in turn needed 63 us for seven rows of
+// 128256 tokens).
 __global__ __launch_bounds__(SB) void k_accept_sampled(SampledAcceptArgs a) {
   __shared__ float red[SW];
   __shared__ int ired[SW];
-  __shared__ float vst[2 * (SAMPLE_SLOTS + 1)];
   __shared__ int acc_s;
+  const float* vst = a.vstats;
   const int k = a.acc.k, V = a.vocab;
   const float it = a.inv_t;
-  for (int j = 0; j <= k; ++j) {
-    const float2 st = a.vgstats ? group_row_stats(a.vgstats + (size_t)j * a.n_groups, a.n_groups, it, red)
-                                : row_stats(a.vlogits + (size_t)j * V, V, it, red);
-    if (threadIdx.x == 0) {
-      vst[2 * j] = st.x;
-      vst[2 * j + 1] = st.y;
-    }
-  }
   if (threadIdx.x == 0) {
     TokenSrc dk = {nullptr, a.acc.dkeys};
     int acc = 0;
@@ -132,12 +143,17 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_sample, dim3(1), dim3(SB), 0, s, a);
+  hipLaunchKernelGGL(k_sample, dim3(a.n_rows), dim3(SB), a.gstats ? 0 : ROW_LDS, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_row_stats(const RowStatsArgs& a, int rows, hipStream_t s) {
+  hipLaunchKernelGGL(k_row_stats, dim3(rows), dim3(SB), a.gstats ? 0 : ROW_LDS, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_accept_sampled(const SampledAcceptArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_accept_sampled, dim3(1), dim3(SB), 0, s, a);
+  hipLaunchKernelGGL(k_accept_sampled, dim3(1), dim3(SB), ROW_LDS, s, a);
   return hipGetLastError();
 }
 

@@ -57,14 +57,22 @@ struct AcceptArgs {
 // exp((z - max) * inv_t)).  Uniforms per step: drafts [0, 16), acceptance
 // tests [16, 32), residual / bonus draw [32].
 constexpr int SAMPLE_SLOTS = 16;
+constexpr int SAMPLE_MAX_ROWS = KEY_PITCH;
 struct SampleArgs {
-  const float* logits; int vocab; float inv_t;
-  const float* u; int u_index;   // the draw uses u[u_index] (u_imm when u is null)
-  float u_imm;
+  int n_rows;                    // draws: row r from logits + r * ld, its key at logical key r of key_out
+  const float* logits; int vocab; int ld; float inv_t;
+  const float* u; int u_index;   // the draw uses u[u_index] (one row), or u_imm[r] when u is null
+  float u_imm[SAMPLE_MAX_ROWS];
   uint64_t* key_out;             // argmax-style key of the drawn token
-  float* stats_out;              // (max, sum) of the row
+  float* stats_out;              // (max, sum) of the row (one row)
   const float2* gstats;          // optional: the row's 16-token group statistics (vocab = 16 n_groups)
   int n_groups;
+};
+struct RowStatsArgs {
+  const float* logits; int ld, vocab; float inv_t;
+  const float2* gstats; int n_groups;  // the rows' 16-token group statistics, or null: from the logits
+  const int32_t* record;               // optional: only rows 0..record[0]
+  float* out;                          // [rows][2]: max, sum of exp((z - max) * inv_t)
 };
 struct SampledAcceptArgs {
   AcceptArgs acc;                // keys, k, commit targets
@@ -73,6 +81,7 @@ struct SampledAcceptArgs {
   const float* vlogits;          // [k+1][vocab]
   int vocab; float inv_t;
   const float* u;                // the step's uniforms
+  const float* vstats;           // [k+1][2] statistics of the verify rows
   const float2* vgstats;         // optional: [k+1][n_groups] group statistics of the verify rows
   int n_groups;
 };
@@ -83,13 +92,14 @@ struct SampledAcceptArgs {
 constexpr int POLICY_TOPK = 5, POLICY_TRACE = 20, POLICY_MAX_DRAFT = 12, POLICY_LOG = 8;
 struct ExitPolicyArgs {
   const float* logits; int vocab;
+  const uint64_t* keys; int key;                   // the row's argmax key: logical key `key` of `keys`
   const float* w1; const float* b1; const float* w2; const float* b2; int hidden;  // fp32, W1 [H][3], W2 [2][H]
   const float* trace; const int32_t* trace_state;  // ring [POLICY_TRACE]; state[0] = count
   float* out;                                      // [POLICY_LOG]: kind, index, C_k, H, C_trace, Q0, Q1, action
   float kind, index;
 };
 struct TracePushArgs {
-  const float* logits; int vocab; int ld;          // rows of logits, row stride
+  const float* stats;                              // [rows][2]: max and sum of exp of the rows' logits
   const int32_t* record;                           // rows = record[0] + 1 when set, else n_rows
   int n_rows;
   float* trace; int32_t* trace_state;              // state[0] = count, state[1] = next slot
@@ -148,6 +158,7 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t s);
 hipError_t launch_sample(const SampleArgs& a, hipStream_t s);
 hipError_t launch_exit_policy(const ExitPolicyArgs& a, hipStream_t s);
 hipError_t launch_trace_push(const TracePushArgs& a, hipStream_t s);
+hipError_t launch_row_stats(const RowStatsArgs& a, int rows, hipStream_t s);
 hipError_t launch_accept_sampled(const SampledAcceptArgs& a, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, int n, hipStream_t s);
 // Reads bytes (a multiple of 16) of src once; e0 / e1 (may be null) bracket

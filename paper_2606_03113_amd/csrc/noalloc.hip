@@ -55,21 +55,22 @@ extern "C" int lede_op_sample_noalloc(const float* logits, int32_t n_rows, int32
   uint64_t* keys = nullptr;
   if (int rc = scratch_address(&keys)) return rc;
   hipStream_t s = (hipStream_t)stream;
-  for (int r = 0; r < n_rows; ++r) {
-    lede::SampleArgs sa{};
-    sa.logits = logits + (size_t)r * ld;
-    sa.vocab = V;
-    sa.inv_t = 1.f / temperature;
-    sa.u = nullptr;
-    sa.u_imm = u[r];
-    sa.key_out = keys + r;
-    sa.stats_out = nullptr;
-    if (lede::launch_sample(sa, s) != hipSuccess) return LEDE_E_HIP;
-  }
-  uint64_t h[KEY_WORDS];
-  if (hipMemcpyAsync(h, keys, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess ||
+  lede::SampleArgs sa{};
+  sa.n_rows = n_rows;
+  sa.logits = logits;
+  sa.vocab = V;
+  sa.ld = ld;
+  sa.inv_t = 1.f / temperature;
+  sa.u = nullptr;
+  for (int r = 0; r < n_rows; ++r) sa.u_imm[r] = u[r];
+  sa.key_out = keys;
+  sa.stats_out = nullptr;
+  if (lede::launch_sample(sa, s) != hipSuccess) return LEDE_E_HIP;
+  // a single writer per key: its first word holds it
+  uint64_t h[NOALLOC_MAX_ROWS];
+  if (hipMemcpyAsync(h, keys, n_rows * sizeof h[0], hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return LEDE_E_HIP;
-  for (int r = 0; r < n_rows; ++r) tokens[r] = lede::key_token(lede::key_value(h, r));
+  for (int r = 0; r < n_rows; ++r) tokens[r] = lede::key_token(h[r]);
   return LEDE_OK;
 }

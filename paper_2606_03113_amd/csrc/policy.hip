@@ -26,23 +26,28 @@ __global__ __launch_bounds__(SB) void k_exit_policy(ExitPolicyArgs a) {
   __shared__ float hid[SB];
   const float* z = a.logits;
   const int V = a.vocab;
-  const int C = chunk_len(V), v0 = threadIdx.x * C, v1 = min(V, v0 + C);
-  // pass 1 over this thread's chunk (batched loads): the max and the top k
-  float m = -INFINITY;
+  const int C = chunk_len(V);
+  // one pass over this thread's chunk: the top k, S = sum e and W = sum e (z - m),
+  // each in index order.  The head's argmax key holds m.
+  const float m = key_logit(key_value(a.keys, a.key));
+  float s_e = 0.f, s_w = 0.f;
   float t[POLICY_TOPK];
 #pragma unroll
   for (int j = 0; j < POLICY_TOPK; ++j) t[j] = -INFINITY;
-  for (int b = v0; b < v1; b += CB) {
+  for (int j0 = 0; j0 < C; j0 += CB) {
     float r[CB];
-    load_batch(z, v1, b, r);
+    load_chunks(z, V, C, j0, r);
+    const int n = chunk_count(V, C, j0);
 #pragma unroll
     for (int j = 0; j < CB; ++j) {
-      const float x = b + j < v1 ? r[j] : -INFINITY;
-      m = fmaxf(m, x);
-      top_insert(t, x);
+      top_insert(t, j < n ? r[j] : -INFINITY);
+      if (j < n) {
+        const float d = r[j] - m, e = expf(d);
+        s_e += e;
+        s_w += e * d;
+      }
     }
   }
-  m = block_max_f(m, red);
   // the top-k lists of a wavefront merged pairwise through shuffles, then
   // the waves' lists by one thread below
 #pragma unroll
@@ -56,19 +61,6 @@ __global__ __launch_bounds__(SB) void k_exit_policy(ExitPolicyArgs a) {
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
     for (int j = 0; j < POLICY_TOPK; ++j) tops[threadIdx.x >> 6][j] = t[j];
-  // pass 2: S = sum e and W = sum e (z - m), each in index order
-  float s_e = 0.f, s_w = 0.f;
-  for (int b = v0; b < v1; b += CB) {
-    float r[CB];
-    load_batch(z, v1, b, r);
-#pragma unroll
-    for (int j = 0; j < CB; ++j)
-      if (b + j < v1) {
-        const float d = r[j] - m, e = expf(d);
-        s_e += e;
-        s_w += e * d;
-      }
-  }
   float S, wtot;
   (void)block_excl_scan(s_e, red, S);
   __syncthreads();
@@ -119,34 +111,32 @@ __global__ __launch_bounds__(SB) void k_exit_policy(ExitPolicyArgs a) {
 }
 
 // Push -log max p (= log S at temperature 1) of each committed row into the
-// window, oldest first.
-__global__ __launch_bounds__(SB) void k_trace_push(TracePushArgs a) {
-  __shared__ float red[SW];
+// window, oldest first (k_row_stats takes the rows side by side; one block that
+// took them in turn needed 10 us for each).
+__global__ __launch_bounds__(64) void k_trace_push(TracePushArgs a) {
   const int n = a.record ? a.record[0] + 1 : a.n_rows;
   // the window as it was, kept so that a failed call can be rolled back
-  static_assert(SB >= POLICY_TRACE, "one thread per slot");
+  static_assert(64 >= POLICY_TRACE, "one thread per slot");
   if (threadIdx.x < POLICY_TRACE) a.backup[threadIdx.x] = a.trace[threadIdx.x];
   if (threadIdx.x < 2) ((int32_t*)(a.backup + POLICY_TRACE))[threadIdx.x] = a.trace_state[threadIdx.x];
   __syncthreads();
-  for (int j = 0; j < n; ++j) {
-    const float2 st = row_stats(a.logits + (size_t)j * a.ld, a.vocab, 1.f, red);
-    if (threadIdx.x == 0) {
-      const int slot = a.trace_state[1];
-      a.trace[slot] = logf(st.y);
-      a.trace_state[1] = (slot + 1) % POLICY_TRACE;
-      a.trace_state[0] = min(a.trace_state[0] + 1, POLICY_TRACE);
-    }
-    __syncthreads();
+  // row j's value goes to slot next + j (at most 16 rows, one lane each)
+  const int slot = a.trace_state[1], count = a.trace_state[0];
+  __syncthreads();
+  if ((int)threadIdx.x < n) a.trace[(slot + threadIdx.x) % POLICY_TRACE] = logf(a.stats[2 * threadIdx.x + 1]);
+  if (threadIdx.x == 0) {
+    a.trace_state[1] = (slot + n) % POLICY_TRACE;
+    a.trace_state[0] = min(count + n, POLICY_TRACE);
   }
 }
 
 hipError_t launch_exit_policy(const ExitPolicyArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_exit_policy, dim3(1), dim3(SB), 0, s, a);
+  hipLaunchKernelGGL(k_exit_policy, dim3(1), dim3(SB), ROW_LDS, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_trace_push(const TracePushArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_trace_push, dim3(1), dim3(SB), 0, s, a);
+  hipLaunchKernelGGL(k_trace_push, dim3(1), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 

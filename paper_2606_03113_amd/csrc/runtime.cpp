@@ -44,6 +44,7 @@ struct Layout {
       record, rope, unif, dstats, trace, trace_state, trace_bak, pol_out, wsbytes;
   // rows of a many-row prefill pass (wide_rows of them; the rest as h .. act, row inputs tiled)
   int wide_rows;
+  size_t rstats;  // [MROWS][2] statistics of logits rows (sampled acceptance, confidence trace)
   size_t wh, wxn, wss, winv, wq, wattn, wact;
   size_t kvbytes, kv_half;
 };
@@ -139,6 +140,7 @@ Layout make_layout(const lede_config* c) {
   o.trace_state = take(4 * 4);
   o.trace_bak = take((POLICY_TRACE + 2) * 4);
   o.pol_out = take((size_t)(c->n_exits + POLICY_MAX_DRAFT) * POLICY_LOG * 4);
+  o.rstats = take(MROWS * 2 * 4);
   o.wide_rows = std::min(WIDE_ROWS, (o.max_ctx + WIDE_ROW_PAD - 1) / WIDE_ROW_PAD * WIDE_ROW_PAD);
   const size_t wr = o.wide_rows;
   o.wh = take(wr * o.d * 4);
@@ -822,7 +824,7 @@ int launch_drafts(lede_ctx* c, int l, int i0, int k, int qnet_after, int pass1_b
     if (rc) return rc;
     if (sampled) {
       SampleArgs sa{};
-      sa.logits = draft_logits(c, i - 1, true); sa.vocab = c->lo.V; sa.inv_t = inv_t;
+      sa.n_rows = 1; sa.logits = draft_logits(c, i - 1, true); sa.vocab = c->lo.V; sa.ld = c->lo.V; sa.inv_t = inv_t;
       sa.u = c->S<float>(c->lo.unif); sa.u_index = i - 1;
       sa.key_out = dk + i; sa.stats_out = c->S<float>(c->lo.dstats) + 2 * (i - 1);
       sa.gstats = logits_gstats(c, MROWS + i - 1); sa.n_groups = c->lo.V / 16;
@@ -834,14 +836,18 @@ int launch_drafts(lede_ctx* c, int l, int i0, int k, int qnet_after, int pass1_b
 }
 
 // Confidence trace of the exit policy: push -log max p of `rows` logits rows
-// (or of record[0] + 1 rows when record is set).
+// (of the first record[0] + 1 of them when record is set).
 int push_trace(lede_ctx* c, const float* logits, int rows, const int32_t* record, hipStream_t s) {
+  RowStatsArgs ra{};
+  ra.logits = logits; ra.ld = ra.vocab = c->lo.V; ra.inv_t = 1.f;
+  ra.record = record; ra.out = c->S<float>(c->lo.rstats);
+  LAUNCH(LEDE_K_ACCEPT, (double)rows * c->lo.V * 4, launch_row_stats(ra, rows, s));
   TracePushArgs ta{};
-  ta.logits = logits; ta.vocab = c->lo.V; ta.ld = c->lo.V;
+  ta.stats = ra.out;
   ta.record = record; ta.n_rows = rows;
   ta.trace = c->S<float>(c->lo.trace); ta.trace_state = c->S<int32_t>(c->lo.trace_state);
   ta.backup = c->S<float>(c->lo.trace_bak);
-  LAUNCH(LEDE_K_ACCEPT, (double)(rows ? rows : 2) * c->lo.V * 4, launch_trace_push(ta, s));
+  LAUNCH(LEDE_K_ACCEPT, (double)rows * 8, launch_trace_push(ta, s));
   c->trace_pushed = true;
   return LEDE_OK;
 }
@@ -888,11 +894,15 @@ int launch_verify(lede_ctx* c, int k, hipStream_t s, float inv_t = 0.f, int from
     sa.vocab = c->lo.V; sa.inv_t = inv_t;
     sa.u = c->S<float>(c->lo.unif);
     sa.vgstats = logits_gstats(c, 0); sa.n_groups = c->lo.V / 16;
+    RowStatsArgs ra{};
+    ra.inv_t = inv_t; ra.gstats = sa.vgstats; ra.n_groups = sa.n_groups; ra.out = c->S<float>(c->lo.rstats);
+    LAUNCH(LEDE_K_ACCEPT, (double)(k + 1) * c->lo.V / 16 * 8, launch_row_stats(ra, k + 1, s));
+    sa.vstats = ra.out;
     LAUNCH(LEDE_K_ACCEPT, (double)(2 * k + 1) * c->lo.V * 4, launch_accept_sampled(sa, s));
   } else {
     LAUNCH(LEDE_K_ACCEPT, 256.0, launch_accept(aa, s));
   }
-  if (trace && (rc = push_trace(c, verify_logits(c, true), 0, aa.record, s))) return rc;
+  if (trace && (rc = push_trace(c, verify_logits(c, true), k + 1, aa.record, s))) return rc;
   c->last_rows = k + 1;
   return LEDE_OK;
 }
@@ -1681,7 +1691,8 @@ static int policy_body(lede_ctx* c, int32_t n_remaining, hipStream_t s, lede_ste
   float* log_dev = c->S<float>(o.pol_out);
   // one decision: the state of the head's logits, scored on the device (kept in
   // the device decision log), read back
-  auto decide = [&](const float* logits, int kind, int index, int* action) -> int {
+  auto decide = [&](const float* logits, int key, int kind, int index, int* action) -> int {
+    pa.keys = dk; pa.key = key;
     pa.out = log_dev + c->policy_log.size();
     pa.logits = logits; pa.kind = (float)kind; pa.index = (float)index;
     PRE();
@@ -1703,7 +1714,7 @@ static int policy_body(lede_ctx* c, int32_t n_remaining, hipStream_t s, lede_ste
       rc = run_layers(c, 1, true, TokenSrc{nullptr, dk}, 0, begin, l, 0, dk + 1, s);
       if (!rc) rc = run_head(c, 1, true, dk + 1, draft_logits(c, 0, true), s);
       int act = 0;
-      if (!rc) rc = decide(draft_logits(c, 0, true), 0, l, &act);
+      if (!rc) rc = decide(draft_logits(c, 0, true), 1, 0, l, &act);
       if (rc) return rc;
       begin = l;
       if (act == 1 || e == c->cfg.n_exits - 1) {
@@ -1717,7 +1728,7 @@ static int policy_body(lede_ctx* c, int32_t n_remaining, hipStream_t s, lede_ste
       rc = run_layers(c, 1, true, TokenSrc{nullptr, dk + k}, k, 0, l_star, 0, dk + k + 1, s, k);
       if (!rc) rc = run_head(c, 1, true, dk + k + 1, draft_logits(c, k, true), s, k);
       int act = 0;
-      if (!rc) rc = decide(draft_logits(c, k, true), 1, k + 1, &act);
+      if (!rc) rc = decide(draft_logits(c, k, true), k + 1, 1, k + 1, &act);
       if (rc) return rc;
       ran_last = act != 1;  // 'continue': this pass was the last draft's input pass
       if (act != 1) break;
@@ -1810,8 +1821,8 @@ int lede_op_sample(const float* logits, int32_t V, float temperature, float u, i
   uint64_t* key = nullptr;
   if (hipMalloc((void**)&key, KEY_WORDS * 8) != hipSuccess) return LEDE_E_HIP;
   SampleArgs sa{};
-  sa.logits = logits; sa.vocab = V; sa.inv_t = 1.f / temperature;
-  sa.u = nullptr; sa.u_imm = u; sa.key_out = key; sa.stats_out = nullptr;
+  sa.n_rows = 1; sa.logits = logits; sa.vocab = sa.ld = V; sa.inv_t = 1.f / temperature;
+  sa.u = nullptr; sa.u_imm[0] = u; sa.key_out = key; sa.stats_out = nullptr;
   uint64_t h = 0;
   int rc = LEDE_OK;
   if (launch_sample(sa, s) != hipSuccess || hipMemcpyAsync(&h, key, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
