@@ -51,7 +51,11 @@ __global__ void k_dqn_init(DqnInitArgs a) {
   }
 }
 
-// One learning update (one block of DQN_THREADS).
+// One learning update (one block of DQN_THREADS).  A chain of short serial
+// sums, bound by LDS latency: the loops are unrolled so that eight elements'
+// reads are in flight, with selects in place of branches, and the loss is
+// summed by a wavefront that has no gradient to sum.  10.3 against 12.3 us at
+// H = 16, B = 32, n = 3.
 __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
   constexpr int PMAX = 6 * DQN_MAX_HIDDEN + 2, NMAX = 2 * DQN_MAX_HIDDEN + 5;
   __shared__ float w_on[PMAX], w_tg[PMAX], grad[PMAX];
@@ -141,6 +145,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
   // Q-values, targets y = R + gamma^n max_a' Qbar(s_{t+n}, a') and TD errors
   for (int b = tid; b < B; b += NT) {
     float o0 = 0.f, o1 = 0.f, t0 = 0.f, t1 = 0.f;
+#pragma unroll 8
     for (int h = 0; h < H; ++h) {
       const float r = fmaxf(pre[b * H + h], 0.f), rt = fmaxf(pre_t[b * H + h], 0.f);
       o0 += w_on[4 * H + h] * r;
@@ -157,8 +162,9 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
   }
   __syncthreads();
   // loss; output-layer gradients; hidden deltas dq W2[a] [pre > 0]
-  if (tid == 0) {
+  if (tid == NT - 1) {
     float L = 0.f;
+#pragma unroll 8
     for (int b = 0; b < B; ++b) L += d2[b];
     a.loss_out[0] = L / (float)B;
   }
@@ -166,13 +172,19 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
     float g = 0.f;
     if (e < 2 * H) {
       const int ac = e / H, h = e % H;
-      for (int b = 0; b < B; ++b)
-        if (act[b] == ac) g += dq[b] * fmaxf(pre[b * H + h], 0.f);
+#pragma unroll 8
+      for (int b = 0; b < B; ++b) {
+        const float gb = g + dq[b] * fmaxf(pre[b * H + h], 0.f);
+        g = act[b] == ac ? gb : g;
+      }
       grad[4 * H + e] = g;
     } else {
       const int ac = e - 2 * H;
-      for (int b = 0; b < B; ++b)
-        if (act[b] == ac) g += dq[b];
+#pragma unroll 8
+      for (int b = 0; b < B; ++b) {
+        const float gb = g + dq[b];
+        g = act[b] == ac ? gb : g;
+      }
       grad[6 * H + ac] = g;
     }
   }
@@ -186,9 +198,11 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
     float g = 0.f;
     if (e < 3 * H) {
       const int h = e / 3, i = e % 3;
+#pragma unroll 8
       for (int b = 0; b < B; ++b) g += pre_t[b * H + h] * sx[b][i];
     } else {
       const int h = e - 3 * H;
+#pragma unroll 8
       for (int b = 0; b < B; ++b) g += pre_t[b * H + h];
     }
     grad[e] = g;
