@@ -24,6 +24,16 @@ __global__ __launch_bounds__(SB) void k_exit_policy(ExitPolicyArgs a) {
   __shared__ float red[SW];
   __shared__ float tops[SW][POLICY_TOPK];
   __shared__ float hid[SB];
+  __shared__ float w2s[2][SB], trs[POLICY_TRACE];
+  static_assert(SB >= 1024, "a thread per hidden unit (at most 1024)");
+  // what the decision reads after the pass, requested before it: a load per
+  // step of a serial sum is a memory round trip each
+  const int tid = threadIdx.x, hc = min(tid, a.hidden - 1);
+  const float w10 = a.w1[hc * 3], w11 = a.w1[hc * 3 + 1], w12 = a.w1[hc * 3 + 2], b1 = a.b1[hc];
+  const float w20 = a.w2[hc], w21 = a.w2[a.hidden + hc];
+  const float b20 = a.b2[0], b21 = a.b2[1];
+  const float trv = a.trace[min(tid, POLICY_TRACE - 1)];
+  const int n_trace = min(a.trace_state[0], POLICY_TRACE);
   const float* z = a.logits;
   const int V = a.vocab;
   const int C = chunk_len(V);
@@ -67,38 +77,48 @@ __global__ __launch_bounds__(SB) void k_exit_policy(ExitPolicyArgs a) {
   (void)block_excl_scan(s_w, red, wtot);
   __syncthreads();
   __shared__ float state[3];
-  if (threadIdx.x == 0) {
-    float t[POLICY_TOPK];
+  w2s[0][tid] = w20;
+  w2s[1][tid] = w21;
+  if (tid < POLICY_TRACE) trs[tid] = trv;
+  if (tid < 64) {  // the wavefronts' lists, one per lane, merged like those of the lanes
 #pragma unroll
-    for (int j = 0; j < POLICY_TOPK; ++j) t[j] = -INFINITY;
-    for (int i = 0; i < SW; ++i)
+    for (int j = 0; j < POLICY_TOPK; ++j) t[j] = tid < SW ? tops[tid][j] : -INFINITY;
 #pragma unroll
-      for (int j = 0; j < POLICY_TOPK; ++j) top_insert(t, tops[i][j]);
+    for (int o = 1; o < SW; o <<= 1) {
+      float u[POLICY_TOPK];
+#pragma unroll
+      for (int j = 0; j < POLICY_TOPK; ++j) u[j] = __shfl_xor(t[j], o);
+#pragma unroll
+      for (int j = 0; j < POLICY_TOPK; ++j) top_insert(t, u[j]);
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
     const int kk = min(POLICY_TOPK, V);
     float ts = 0.f;
-    for (int j = 0; j < kk; ++j) ts += t[j] - m;
+#pragma unroll
+    for (int j = 0; j < POLICY_TOPK; ++j)
+      if (j < kk) ts += t[j] - m;
     const float logS = logf(S);
-    const int n = min(a.trace_state[0], POLICY_TRACE);
+    const int n = n_trace;
     float tr = 0.f;
-    for (int i = 0; i < n; ++i) tr += a.trace[i];
+#pragma unroll
+    for (int i = 0; i < POLICY_TRACE; ++i)
+      if (i < n) tr += trs[i];
     state[0] = logS - ts / (float)kk;
     state[1] = logS - wtot / S;
     state[2] = n ? tr / (float)n : 0.f;
   }
   __syncthreads();
-  for (int h = threadIdx.x; h < a.hidden; h += SB) {
-    float x = a.b1[h];
-    for (int i = 0; i < 3; ++i) x = fmaf(a.w1[h * 3 + i], state[i], x);
-    hid[h] = fmaxf(x, 0.f);
-  }
+  hid[tid] = fmaxf(fmaf(w12, state[2], fmaf(w11, state[1], fmaf(w10, state[0], b1))), 0.f);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float q[2];
-    for (int o = 0; o < 2; ++o) {
-      float x = a.b2[o];
-      for (int h = 0; h < a.hidden; ++h) x = fmaf(a.w2[o * a.hidden + h], hid[h], x);
-      q[o] = x;
-    }
+  if (tid < 64) {  // lane o sums output o in order
+    const int o = tid & 1;
+    float x = o ? b21 : b20;
+#pragma unroll 8
+    for (int h = 0; h < a.hidden; ++h) x = fmaf(w2s[o][h], hid[h], x);
+    const float q[2] = {__shfl(x, 0), __shfl(x, 1)};
+    if (tid != 0) return;
     a.out[0] = a.kind;
     a.out[1] = a.index;
     a.out[2] = state[0];
