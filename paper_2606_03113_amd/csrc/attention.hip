@@ -24,13 +24,33 @@ __device__ __forceinline__ void load8(const void* base, size_t idx, float* o) {
   }
 }
 
+// One step of the page-ordered combine: fold a page's (max, sum, weighted
+// value) into the running (mx, l, acc).
+__device__ __forceinline__ void fold_step(float& mx, float& l, float& acc, float pm, float pl, float pa) {
+  const float nm = fmaxf(mx, pm);
+  const float so = (mx == -INFINITY) ? 0.f : __expf(mx - nm);
+  const float sn = __expf(pm - nm);
+  l = fmaf(pl, sn, l * so);  // (spelled out: the kernels that fold must round alike)
+  acc = fmaf(pa, sn, acc * so);
+  mx = nm;
+}
+
+// Attention output element (row m, column col of nq * hd).
+template <int DT>
+__device__ __forceinline__ void store_out(const AttnArgs& a, int m, int col, float v) {
+  if (a.KT_tiled) Elem<DT>::store((uint8_t*)a.out + tiled_row_off<DT>(m, col, a.KT_tiled), 0, v);
+  else Elem<DT>::store(a.out, (size_t)m * a.ldo + col, v);
+}
+
 // Partial attention of up to 16 query rows (row = (m, query head of the
 // group)) against whole 64-token pages; pages are strided over the blocks of
 // a split.  For every (row, page): running max, sum of exp and the
 // exp-weighted value sum, stored for the combine kernel.  A row's partials
 // do not depend on which other rows share the block.
-template <int DT, int HD>
-__global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
+// SHORT: one block takes every page and folds the partials itself, in page
+// order as the combine kernel does up to 16 pages, and stores the result.
+template <int DT, int HD, bool SHORT>
+__device__ __forceinline__ void attn_partial(const AttnArgs& a) {
   constexpr int NPC = HD / 32;  // 8-element pieces per thread in the score phase
   constexpr int PV_DG = HD / 8, PV_TG = 256 / PV_DG, TPT = 64 / PV_TG;
   __shared__ float qs[16][HD];
@@ -85,6 +105,10 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
   }
   __syncthreads();
 
+  constexpr int NF = 16 * HD / 256;  // SHORT: elements (row, dim) of a thread
+  float fm[NF], fl[NF], fa[NF];
+#pragma unroll
+  for (int k = 0; k < NF; ++k) fm[k] = -INFINITY, fl[k] = fa[k] = 0.f;
   for (int j = blockIdx.y; j < n_chunks; j += a.n_split) {
     const int tok0 = j * 64;
     {
@@ -136,6 +160,16 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
     }
     __syncthreads();
     if (j + a.n_split < n_chunks) load_page(j + a.n_split);  // the next page of this block
+    if (SHORT) {
+#pragma unroll
+      for (int k = 0; k < NF; ++k) {
+        const int idx = tid + 256 * k, r = idx / HD, i = idx % HD;
+        if (r < nr && j <= (pos0 + (r0 + r) / G) / 64)
+          fold_step(fm[k], fl[k], fa[k], st_m[r], st_l[r], ((red[0][r][i] + red[1][r][i]) + red[2][r][i]) + red[3][r][i]);
+      }
+      __syncthreads();
+      continue;
+    }
     for (int idx = tid; idx < nr * HD; idx += 256) {
       const int r = idx / HD, i = idx % HD;
       const int rr = r0 + r, m = rr / G, head = kvh * G + rr % G;
@@ -148,17 +182,21 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
     }
     __syncthreads();
   }
+  if (SHORT) {
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+      const int idx = tid + 256 * k, r = idx / HD, i = idx % HD, rr = r0 + r;
+      if (r < nr) store_out<DT>(a, rr / G, (kvh * G + rr % G) * HD + i, fa[k] / fl[k]);
+    }
+  }
 }
-
-// One step of the page-ordered combine: fold a page's (max, sum, weighted
-// value) into the running (mx, l, acc).
-__device__ __forceinline__ void fold_step(float& mx, float& l, float& acc, float pm, float pl, float pa) {
-  const float nm = fmaxf(mx, pm);
-  const float so = (mx == -INFINITY) ? 0.f : __expf(mx - nm);
-  const float sn = __expf(pm - nm);
-  l = fmaf(pl, sn, l * so);  // (spelled out: the kernels that fold must round alike)
-  acc = fmaf(pa, sn, acc * so);
-  mx = nm;
+template <int DT, int HD>
+__global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
+  attn_partial<DT, HD, false>(a);
+}
+template <int DT, int HD>
+__global__ __launch_bounds__(256) void k_attn_short(AttnArgs a) {
+  attn_partial<DT, HD, true>(a);
 }
 
 // Combine the per-page partials of every (row, head): S = blockDim / HD
@@ -203,10 +241,7 @@ __global__ __launch_bounds__(HD * COMBINE_GROUPS) void k_attn_combine(AttnArgs a
   __syncthreads();
   if (sg == 0) {
     for (int q = 1; q < S && q * B < nc; ++q) fold_step(mx, l, acc, st[q][0][i], st[q][1][i], st[q][2][i]);
-    if (a.KT_tiled)
-      Elem<DT>::store((uint8_t*)a.out + tiled_row_off<DT>(m, head * HD + i, a.KT_tiled), 0, acc / l);
-    else
-      Elem<DT>::store(a.out, (size_t)m * a.ldo + head * HD + i, acc / l);
+    store_out<DT>(a, m, head * HD + i, acc / l);
   }
 }
 
@@ -232,10 +267,9 @@ __device__ __forceinline__ void split8(const float* x, uint4& hi, uint4& lo) {
 // same way; the wavefront's value columns are staged in LDS and read back
 // transposed).  Every output element is a fixed-order function of its own
 // row, so a row's partials do not depend on the rows sharing its block.
-// Five waves per SIMD (at most 96 VGPRs, no spills) keeps five blocks per
-// CU instead of four.
-template <int HD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_attn_mfma(AttnArgs a) {
+// SHORT: as in attn_partial.
+template <int HD, bool SHORT>
+__device__ __forceinline__ void attn_mfma(const AttnArgs& a) {
   constexpr int KS = HD / 32;          // k-steps of the scores
   constexpr int DW = HD / 4;           // output dims per wavefront
   constexpr int DT = DW / 16;          // 16-dim output tiles per wavefront
@@ -282,6 +316,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   }
   const uint16_t* kc = (const uint16_t*)a.kcache;
   const uint16_t* vc = (const uint16_t*)a.vcache;
+  float fm[DT][4], fl[DT][4], fa[DT][4];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fm[dt][i] = -INFINITY, fl[dt][i] = fa[dt][i] = 0.f;
   for (int j = blockIdx.y; j < n_chunks; j += a.n_split) {
     const int page = a.block_table[j];
     const size_t base = (((size_t)a.layer * a.n_pages + page) * a.nkv + kvh) * 64 * HD;
@@ -374,7 +413,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
       }
     }
     // partials of row lr: dims w * DW + 16 dt + 4 lg + i
-    if (row_ok) {
+    if (SHORT) {
+      const float pl = ((ssum[0][lr] + ssum[1][lr]) + ssum[2][lr]) + ssum[3][lr];
+      if (j <= row_pos / 64)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fold_step(fm[dt][i], fl[dt][i], fa[dt][i], pm, pl, oc[dt][i]);
+    } else if (row_ok) {
       float* p = a.part + (((size_t)m_row * a.nq + head) * a.max_chunks + j) * (HD + 2);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
@@ -389,6 +435,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     }
     __syncthreads();  // the next page rewrites the staging
   }
+  if (SHORT && row_ok) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) store_out<1>(a, m_row, head * HD + w * DW + 16 * dt + 4 * lg + i, fa[dt][i] / fl[dt][i]);
+  }
+}
+// Five waves per SIMD (at most 96 VGPRs, no spills) keeps five blocks per
+// CU instead of four.
+template <int HD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_attn_mfma(AttnArgs a) {
+  attn_mfma<HD, false>(a);
+}
+template <int HD>
+__global__ __launch_bounds__(256) void k_attn_mfma_short(AttnArgs a) {
+  attn_mfma<HD, true>(a);
 }
 
 // The sum (or maximum) of the values of lanes l and l ^ X, X = 16 or 32, as
@@ -619,30 +681,28 @@ hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s) {
   return hipLaunchKernel(f, grid, dim3(512), args, lds, s);
 }
 
-hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
-  const int G = a.nq / a.nkv;
-  const int n_rs = (a.M * G + a.rows_per_block - 1) / a.rows_per_block;
-  dim3 grid(a.nkv * n_rs, a.n_split);
-  const int combine_grid = a.M * a.nq;
+template <int DT, int HD>
+static void launch_attention_t(const AttnArgs& a, hipStream_t s) {
+  const int n_rs = (a.M * (a.nq / a.nkv) + a.rows_per_block - 1) / a.rows_per_block;
+  const dim3 grid(a.nkv * n_rs, a.n_split);
+  if (a.short_ctx) {
+    if (DT == 1 && a.mfma) hipLaunchKernelGGL((k_attn_mfma_short<HD>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_attn_short<DT, HD>), grid, dim3(256), 0, s, a);
+    return;
+  }
+  if (DT == 1 && a.mfma) hipLaunchKernelGGL((k_attn_mfma<HD>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_attn_partial<DT, HD>), grid, dim3(256), 0, s, a);
   const int groups = (a.max_chunks + 15) / 16 < COMBINE_GROUPS ? (a.max_chunks + 15) / 16 : COMBINE_GROUPS;
+  hipLaunchKernelGGL((k_attn_combine<DT, HD>), dim3(a.M * a.nq), dim3(HD * groups), 0, s, a);
+}
+
+hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
   if (dtype == 1) {
-    if (a.hd == 128) {
-      if (a.mfma) hipLaunchKernelGGL((k_attn_mfma<128>), grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL((k_attn_partial<1, 128>), grid, dim3(256), 0, s, a);
-      hipLaunchKernelGGL((k_attn_combine<1, 128>), dim3(combine_grid), dim3(128 * groups), 0, s, a);
-    } else {
-      if (a.mfma) hipLaunchKernelGGL((k_attn_mfma<64>), grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL((k_attn_partial<1, 64>), grid, dim3(256), 0, s, a);
-      hipLaunchKernelGGL((k_attn_combine<1, 64>), dim3(combine_grid), dim3(64 * groups), 0, s, a);
-    }
+    if (a.hd == 128) launch_attention_t<1, 128>(a, s);
+    else launch_attention_t<1, 64>(a, s);
   } else {
-    if (a.hd == 128) {
-      hipLaunchKernelGGL((k_attn_partial<0, 128>), grid, dim3(256), 0, s, a);
-      hipLaunchKernelGGL((k_attn_combine<0, 128>), dim3(combine_grid), dim3(128 * groups), 0, s, a);
-    } else {
-      hipLaunchKernelGGL((k_attn_partial<0, 64>), grid, dim3(256), 0, s, a);
-      hipLaunchKernelGGL((k_attn_combine<0, 64>), dim3(combine_grid), dim3(64 * groups), 0, s, a);
-    }
+    if (a.hd == 128) launch_attention_t<0, 128>(a, s);
+    else launch_attention_t<0, 64>(a, s);
   }
   return hipGetLastError();
 }

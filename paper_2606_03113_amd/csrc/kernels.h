@@ -29,6 +29,7 @@ struct AttnArgs {
   const int32_t* block_table; const int32_t* seq_len; int pos_off;
   int n_split;                     // blocks per (kv head, row slice); chunks strided
   int rows_per_block;              // <= 16 query rows (m, head-in-group) per block
+  int short_ctx;                   // at most 16 pages, all taken by one block per (kv head, row slice), which folds them itself (n_split 1)
   int max_chunks;
   float* part;                     // [M][nq][max_chunks][hd + 2]
   void* out; int ldo;              // combine output [M][nq*hd], model dtype
@@ -169,6 +170,7 @@ hipError_t launch_read_probe(const void* src, size_t bytes, uint32_t* sink, int 
 // linear kernel's load structure, one group per block.
 hipError_t launch_read_groups(const void* src, int n_groups, int tiles, uint32_t* sink, hipStream_t s,
                               hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+hipError_t launch_commit_prefill(const uint64_t* vkeys, int row, uint64_t* dkeys, int32_t* seq_len, int len, hipStream_t s);
 hipError_t launch_set_token(uint64_t* keys, int idx, int token, hipStream_t s);
 hipError_t launch_dqn_init(const DqnInitArgs& a, hipStream_t s);
 hipError_t launch_dqn_update(const DqnUpdateArgs& a, hipStream_t s);

@@ -69,6 +69,14 @@ __global__ void k_fill_u64(uint64_t* p, uint64_t v, int n) {
   if (i < n) p[i] = v;
 }
 
+// End of a prefill: the argmax of row `row` becomes the pending token, and the
+// committed length len.
+__global__ void k_commit_prefill(const uint64_t* vkeys, int row, uint64_t* dkeys, int32_t* seq_len, int len) {
+  if (threadIdx.x != 0) return;
+  key_store_token(dkeys, 0, key_token(key_value(vkeys, row)));
+  *seq_len = len;
+}
+
 __global__ void k_set_token(uint64_t* keys, int idx, int token) {
   if (threadIdx.x == 0) key_store_token(keys, idx, token);
 }
@@ -158,6 +166,12 @@ hipError_t launch_read_groups(const void* src, int n_groups, int tiles, uint32_t
 
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, int n, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_u64, dim3((n + 255) / 256), dim3(256), 0, s, p, v, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_commit_prefill(const uint64_t* vkeys, int row, uint64_t* dkeys, int32_t* seq_len, int len,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL(k_commit_prefill, dim3(1), dim3(64), 0, s, vkeys, row, dkeys, seq_len, len);
   return hipGetLastError();
 }
 

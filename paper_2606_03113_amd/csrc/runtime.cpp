@@ -24,6 +24,7 @@ namespace {
 
 constexpr int PAGE = 64;
 constexpr int MROWS = 16;   // rows of one verify / prefill pass
+constexpr int SHORT_PAGES = 2;   // contexts whose attention runs in one kernel
 constexpr int WIDE_ROWS = 2048;  // rows of one prefill pass of the many-row kernels, at most
 static_assert(MROWS <= KEY_PITCH && 15 + 2 <= KEY_PITCH, "a key buffer holds every row's key and every draft's");
 constexpr int RECORD_INTS = 64;
@@ -524,6 +525,12 @@ AttnArgs attn_args(const lede_ctx* c, int j, int M, bool vec, int pos_off) {
   // step with 512 blocks of five pages; shorter contexts have a page per
   // block either way
   at.n_split = std::max(1, std::min(o.max_chunks, (2048 + o.nkv * n_rs - 1) / (o.nkv * n_rs)));
+  // contexts of at most two pages: one kernel, a block per KV head and row
+  // slice folding its own pages.  The positions are the host's upper bound;
+  // a captured step is replayed at any length.
+  const int len = c->use_graphs ? o.max_ctx : (c->inflight.empty() ? c->seq_len : c->seq_ub) + pos_off + M;
+  at.short_ctx = len <= SHORT_PAGES * PAGE;
+  if (at.short_ctx) at.n_split = 1;
   at.max_chunks = o.max_chunks;
   at.part = c->S<float>(o.part);
   // bf16 partials on the matrix cores for every multi-row pass (verify,
@@ -1247,7 +1254,7 @@ static int prefill_impl(lede_ctx* c, const int32_t* tokens, int32_t n, hipStream
   const int c0 = c->seq_len;
   int rc = ensure_pages(c, c0 + n);
   if (rc) return rc;
-  if ((rc = upload_table(c, s)) || (rc = upload_seq_len(c, c0, s))) return rc;
+  if ((rc = upload_table(c, s))) return rc;  // (the device's length is the committed one)
   int32_t* pd = c->S<int32_t>(c->lo.prompt);
   PRE();
   HIP_CHECK(c, hipMemcpyAsync(pd, tokens, (size_t)n * 4, hipMemcpyHostToDevice, s));
@@ -1268,13 +1275,13 @@ static int prefill_impl(lede_ctx* c, const int32_t* tokens, int32_t n, hipStream
   if ((rc = run_head(c, last_m, false, vk, verify_logits(c, trace), s, 0, true))) return rc;
   if (trace && (rc = push_trace(c, verify_logits(c, true) + (size_t)(last_m - 1) * c->lo.V, 1, nullptr, s))) return rc;
   c->last_rows = last_m;
+  // the device commits the pending token and the length; one read-back
   PRE();
-  HIP_CHECK(c, hipMemcpyAsync(c->keys_h, vk, KEY_WORDS * 8, hipMemcpyDeviceToHost, s));
+  HIP_CHECK(c, launch_commit_prefill(vk, last_m - 1, c->S<uint64_t>(c->lo.dkeys), c->S<int32_t>(c->lo.seq_len), c0 + n, s));
+  PRE();
+  HIP_CHECK(c, hipMemcpyAsync(c->keys_h, c->S<uint64_t>(c->lo.dkeys), 8, hipMemcpyDeviceToHost, s));
   HIP_CHECK(c, hipStreamSynchronize(s));
-  const int next = key_token(key_value(c->keys_h, last_m - 1));
-  PRE();
-  HIP_CHECK(c, launch_set_token(c->S<uint64_t>(c->lo.dkeys), 0, next, s));
-  if ((rc = upload_seq_len(c, c0 + n, s))) return rc;
+  const int next = key_token(c->keys_h[0]);
   c->seq_len = c0 + n;
   c->pending = next;
   if (next_token) *next_token = next;
