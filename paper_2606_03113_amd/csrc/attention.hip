@@ -472,9 +472,10 @@ __device__ __forceinline__ float pair_lanes(float v) {
 // the order of k_attn_combine: pages in order within the runs of 16 that one
 // of its thread groups folds, then the groups in order.  So a row has the bits
 // of the two kernels at any row count, without their partials in memory.
-// Bound by the vector work beside the products (exponentials, the bf16 splits,
-// the fold): 2048 rows of the Llama-2-13B shape take 302 us a layer, against
-// 2180 for the two kernels 16 rows at a time; 97 rows 17 against 74.
+// Bound by the chain within a page (products, maximum, exponentials, products:
+// about 2.7 us with one or two wavefronts per SIMD, and the same with pages
+// fetched two ahead): 2048 rows of the Llama-2-13B shape take 194 us a layer,
+// against 2180 for the two kernels 16 rows at a time; 97 rows 13 against 74.
 template <int HD>
 __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   constexpr int KS = HD / 32, NT = HD / 16;  // k-steps of the scores, output tiles
@@ -570,16 +571,24 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
     if (j < nc_wave) {
       const bool ends = j >= nc_full;  // some row of the wavefront ends in or before this page
       // S^T tiles: lane holds tokens 16 tg + 4 lg + i of row lr
+      // (products of different tiles side by side: one tile's are a chain)
       float pv[4][4], mx = -INFINITY;
+      f32x4 sc4[4];
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) sc4[tg] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s2 = 0; s2 < KS; ++s2) {
+        uint4 kf[4];
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) kf[tg] = lds_ld16(kb + (buf * KT + tg * KS + s2) * 1024 + l * 16);
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) sc4[tg] = mfma_tile<1>(kf[tg], qh[s2], sc4[tg]);
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) sc4[tg] = mfma_tile<1>(kf[tg], ql[s2], sc4[tg]);
+      }
 #pragma unroll
       for (int tg = 0; tg < 4; ++tg) {
-        f32x4 sc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s2 = 0; s2 < KS; ++s2) {
-          const uint4 kf = lds_ld16(kb + (buf * KT + tg * KS + s2) * 1024 + l * 16);
-          sc = mfma_tile<1>(kf, qh[s2], sc);
-          sc = mfma_tile<1>(kf, ql[s2], sc);
-        }
+        const f32x4 sc = sc4[tg];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int t = j * 64 + 16 * tg + 4 * lg + i;
@@ -629,16 +638,25 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
       gl = fmaf(pl, sn, gl * so);
       gm = nm;
 #pragma unroll
-      for (int d = 0; d < NT; ++d) {
-        f32x4 oc = {0.f, 0.f, 0.f, 0.f};
+      for (int d0 = 0; d0 < NT; d0 += 4) {
+        f32x4 oc[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) oc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-          const uint4 vt = lds_ld16((const uint8_t*)&vb[(buf * HD + 16 * d + lr) * VS + 16 * ks + 4 * lg]);
-          oc = mfma_tile<1>(vt, ph[ks], oc);
-          oc = mfma_tile<1>(vt, po[ks], oc);
+          uint4 vt[4];
+#pragma unroll
+          for (int d = 0; d < 4; ++d)
+            vt[d] = lds_ld16((const uint8_t*)&vb[(buf * HD + 16 * (d0 + d) + lr) * VS + 16 * ks + 4 * lg]);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) oc[d] = mfma_tile<1>(vt[d], ph[ks], oc[d]);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) oc[d] = mfma_tile<1>(vt[d], po[ks], oc[d]);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) ga[d][i] = fmaf(oc[i], sn, ga[d][i] * so);
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) ga[d0 + d][i] = fmaf(oc[d][i], sn, ga[d0 + d][i] * so);
       }
     }
     const int sg = (j >> 4) % S;
