@@ -63,10 +63,11 @@ __global__ __launch_bounds__(SB) void k_sample(SampleArgs a) {
     st.x = block_max_f(ch.max(), red);
     tok = draw_group(ch, ch.sum(st.x, it), z, st.x, it, u, st.y, red, ired);
   } else {
-    float s;
-    st.x = row_max_sum(z, a.vocab, it, s, red);
+    float s, w[2][CB];
+    st.x = row_max_sum(z, a.vocab, it, s, w, red);
     const float m = st.x;
-    tok = draw_chunk([&](float x, float) { return expf((x - m) * it); }, s, z, nullptr, a.vocab, u, st.y, red, ired);
+    if (chunk_len(a.vocab) <= 2 * CB) tok = draw_held(w, s, a.vocab, u, st.y, red, ired);
+    else tok = draw_chunk([&](float x, float) { return expf((x - m) * it); }, s, z, nullptr, a.vocab, u, st.y, red, ired);
   }
   if (threadIdx.x == 0) {
     key_store_token(a.key_out, row, tok);

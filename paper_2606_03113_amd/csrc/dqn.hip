@@ -19,13 +19,19 @@ __device__ __forceinline__ float noise_f(float x) { return copysignf(sqrtf(fabsf
 
 // Noise of parameter p of a set, from the f-values of one draw laid out as
 // f(eps_in1) [3], f(eps_out1) [H], f(eps_in2) [H], f(eps_out2) [2].
-__device__ __forceinline__ float noise_of(const float* nf, int H, int p) {
+// x / H for 0 <= x < 4096, 1 <= H <= 128, by HM = ceil(2^19 / H): the error
+// x (HM H - 2^19) stays below 2^19.
+__device__ __forceinline__ int div_h(int x, int HM) { return (x * HM) >> 19; }
+__device__ __forceinline__ float noise_of(const float* nf, int H, int HM, int p) {
   const float *fi1 = nf, *fo1 = nf + 3, *fi2 = nf + 3 + H, *fo2 = nf + 3 + 2 * H;
   if (p < 3 * H) return fo1[p / 3] * fi1[p % 3];
   p -= 3 * H;
   if (p < H) return fo1[p];
   p -= H;
-  if (p < 2 * H) return fo2[p / H] * fi2[p % H];
+  if (p < 2 * H) {
+    const int o = div_h(p, HM);
+    return fo2[o] * fi2[p - o * H];
+  }
   return fo2[p - 2 * H];
 }
 
@@ -66,6 +72,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
   __shared__ int act[DQN_MAX_BATCH], boot[DQN_MAX_BATCH];
   const int tid = threadIdx.x, NT = DQN_THREADS;
   const int H = a.H, B = a.B, P = dqn_params(H), NC = dqn_noise(H);
+  const int HM = ((1 << 19) + H - 1) / H;
   // parameter p = tid + NT i of a set: its mean and scale, their Adam
   // moments and the target's, all requested up front (one round trip)
   constexpr int PI = (6 * DQN_MAX_HIDDEN + 2 + DQN_THREADS - 1) / DQN_THREADS;
@@ -95,8 +102,8 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
   for (int i = 0; i < PI; ++i) {
     const int p = tid + NT * i;
     if (p < P) {
-      w_on[p] = th_mu[i] + th_sg[i] * noise_of(nf_on, H, p);
-      w_tg[p] = tg_mu[i] + tg_sg[i] * noise_of(nf_tg, H, p);
+      w_on[p] = th_mu[i] + th_sg[i] * noise_of(nf_on, H, HM, p);
+      w_tg[p] = tg_mu[i] + tg_sg[i] * noise_of(nf_tg, H, HM, p);
     }
   }
   // sampled transitions: position floor(m * n_valid / 2^24) of the stored
@@ -106,7 +113,9 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
     const float x = fminf(fmaxf(a.u[b] * 16777216.f, 0.f), 16777215.f);
     const uint64_t mq = (uint64_t)(uint32_t)x;
     const int j = (int)((mq * (uint64_t)a.n_valid) >> 24);
-    const float* s0 = a.ring + (size_t)((a.oldest + j) % a.capacity) * DQN_SLOT;
+    // slots from the sample's on, wrapping (oldest and j are below capacity)
+    const int q0 = a.oldest + j - (a.oldest + j >= a.capacity ? a.capacity : 0);
+    const float* s0 = a.ring + (size_t)q0 * DQN_SLOT;
     sx[b][0] = s0[0];
     sx[b][1] = s0[1];
     sx[b][2] = s0[2];
@@ -114,9 +123,13 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
     // every reward and terminal flag of the window is requested before the
     // first is used (one round trip), then folded in order
     float2 rd[DQN_MAX_N];
+    int q = q0;
 #pragma unroll
     for (int k = 0; k < DQN_MAX_N; ++k)
-      if (k < a.n) rd[k] = *(const float2*)(a.ring + (size_t)((a.oldest + j + k) % a.capacity) * DQN_SLOT + 4);
+      if (k < a.n) {
+        rd[k] = *(const float2*)(a.ring + (size_t)q * DQN_SLOT + 4);
+        q = q + 1 == a.capacity ? 0 : q + 1;
+      }
     float R = 0.f, gk = 1.f;
     int bt = 1;
 #pragma unroll
@@ -129,7 +142,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
     }
     ret[b] = R;
     boot[b] = bt;
-    const float* s1 = a.ring + (size_t)((a.oldest + j + a.n) % a.capacity) * DQN_SLOT;
+    const float* s1 = a.ring + (size_t)q * DQN_SLOT;
     sn[b][0] = bt ? s1[0] : 0.f;
     sn[b][1] = bt ? s1[1] : 0.f;
     sn[b][2] = bt ? s1[2] : 0.f;
@@ -137,7 +150,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
   __syncthreads();
   // hidden pre-activations W1 s + b1 (online on s_t, target on s_{t+n})
   for (int e = tid; e < B * H; e += NT) {
-    const int b = e / H, h = e % H;
+    const int b = div_h(e, HM), h = e - b * H;
     pre[e] = w_on[3 * h] * sx[b][0] + w_on[3 * h + 1] * sx[b][1] + w_on[3 * h + 2] * sx[b][2] + w_on[3 * H + h];
     pre_t[e] = w_tg[3 * h] * sn[b][0] + w_tg[3 * h + 1] * sn[b][1] + w_tg[3 * h + 2] * sn[b][2] + w_tg[3 * H + h];
   }
@@ -171,7 +184,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
   for (int e = tid; e < 2 * H + 2; e += NT) {
     float g = 0.f;
     if (e < 2 * H) {
-      const int ac = e / H, h = e % H;
+      const int ac = div_h(e, HM), h = e - ac * H;
 #pragma unroll 8
       for (int b = 0; b < B; ++b) {
         const float gb = g + dq[b] * fmaxf(pre[b * H + h], 0.f);
@@ -189,7 +202,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
     }
   }
   for (int e = tid; e < B * H; e += NT) {
-    const int b = e / H, h = e % H;
+    const int b = div_h(e, HM), h = e - b * H;
     pre_t[e] = pre[e] > 0.f ? dq[b] * w_on[4 * H + act[b] * H + h] : 0.f;
   }
   __syncthreads();
@@ -224,7 +237,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_update(DqnUpdateArgs a) {
     if (p < P) {
       const float g = grad[p];
       adam(g, th_mu[i], m_mu[i], v_mu[i], p);
-      adam(g * noise_of(nf_on, H, p), th_sg[i], m_sg[i], v_sg[i], (size_t)P + p);
+      adam(g * noise_of(nf_on, H, HM, p), th_sg[i], m_sg[i], v_sg[i], (size_t)P + p);
     }
   }
 }
@@ -281,7 +294,7 @@ __global__ __launch_bounds__(DQN_THREADS) void k_dqn_act(DqnActArgs a) {
   for (int i = threadIdx.x; i < NC; i += DQN_THREADS) nf[i] = a.noise ? noise_f(a.noise[i]) : 0.f;
   __syncthreads();
   for (int p = threadIdx.x; p < P; p += DQN_THREADS) {
-    const float w = a.noise ? a.theta[p] + a.theta[P + p] * noise_of(nf, H, p) : a.theta[p];
+    const float w = a.noise ? a.theta[p] + a.theta[P + p] * noise_of(nf, H, ((1 << 19) + H - 1) / H, p) : a.theta[p];
     if (p < 3 * H) a.w1[p] = w;
     else if (p < 4 * H) a.b1[p - 3 * H] = w;
     else if (p < 6 * H) a.w2[p - 4 * H] = w;

@@ -169,6 +169,33 @@ __device__ int draw_chunk(F f, float s, const float* z1, const float* z2, int V,
   __syncthreads();
   return tok;
 }
+// The same from the weights of chunks of at most 2 CB tokens, held by their
+// threads.
+__device__ inline int draw_held(const float (&w)[2][CB], float s, int V, float u, float& total, float* red, int* ired) {
+  const float pre = block_excl_scan(s, red, total);
+  const float thr = u * total;
+  const int owner = block_max_i((s > 0.f && pre <= thr) ? (int)threadIdx.x : -1, ired);
+  __shared__ int tok;
+  if ((int)threadIdx.x == owner) {
+    const int C = chunk_len(V), v0 = owner * C, n = min(C, V - v0);
+    float acc = pre;
+    int hit = -1, last = -1;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int j = 0; j < CB; ++j)
+        if (q * CB + j < n && hit < 0) {
+          if (w[q][j] > 0.f) last = v0 + q * CB + j;
+          acc += w[q][j];
+          if (acc > thr) hit = v0 + q * CB + j;
+        }
+    tok = hit >= 0 ? hit : last;
+  }
+  if (threadIdx.x == 0 && owner < 0) tok = -1;
+  __syncthreads();
+  return tok;
+}
+
 template <typename F>
 __device__ int block_draw(F f, const float* z1, const float* z2, int V, float u, float* red, int* ired) {
   float total;
@@ -176,13 +203,13 @@ __device__ int block_draw(F f, const float* z1, const float* z2, int V, float u,
 }
 
 // The row's maximum, and this thread's chunk sum of exp((z - max) * inv_t).
-// Rows of up to 2 CB SB tokens are read once.
-__device__ inline float row_max_sum(const float* z, int V, float inv_t, float& s, float* red) {
+// Rows of up to 2 CB SB tokens (chunks of at most 2 CB) are read once, and r
+// then holds the weights.
+__device__ inline float row_max_sum(const float* z, int V, float inv_t, float& s, float (&r)[2][CB], float* red) {
   const int C = chunk_len(V);
   float m = -INFINITY;
   s = 0.f;
   if (C <= 2 * CB) {
-    float r[2][CB];
     const int n[2] = {chunk_count(V, C, 0), chunk_count(V, C, CB)};
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -195,8 +222,10 @@ __device__ inline float row_max_sum(const float* z, int V, float inv_t, float& s
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int j = 0; j < CB; ++j)
-        if (j < n[q]) s += expf((r[q][j] - m) * inv_t);
+      for (int j = 0; j < CB; ++j) {
+        r[q][j] = expf((r[q][j] - m) * inv_t);
+        if (j < n[q]) s += r[q][j];
+      }
   } else {
     for (int j0 = 0; j0 < C; j0 += CB) {
       float r[CB];
@@ -214,8 +243,8 @@ __device__ inline float row_max_sum(const float* z, int V, float inv_t, float& s
 
 // (max, sum of exp((z - max) * inv_t)) of one row.
 __device__ inline float2 row_stats(const float* z, int V, float inv_t, float* red) {
-  float s, total;
-  const float m = row_max_sum(z, V, inv_t, s, red);
+  float s, total, r[2][CB];
+  const float m = row_max_sum(z, V, inv_t, s, r, red);
   (void)block_excl_scan(s, red, total);
   __syncthreads();
   return make_float2(m, total);
