@@ -24,7 +24,6 @@ namespace {
 
 constexpr int PAGE = 64;
 constexpr int MROWS = 16;   // rows of one verify / prefill pass
-constexpr int SHORT_PAGES = 2;   // contexts whose attention runs in one kernel
 constexpr int WIDE_ROWS = 2048;  // rows of one prefill pass of the many-row kernels, at most
 static_assert(MROWS <= KEY_PITCH && 15 + 2 <= KEY_PITCH, "a key buffer holds every row's key and every draft's");
 constexpr int RECORD_INTS = 64;
@@ -525,11 +524,16 @@ AttnArgs attn_args(const lede_ctx* c, int j, int M, bool vec, int pos_off) {
   // step with 512 blocks of five pages; shorter contexts have a page per
   // block either way
   at.n_split = std::max(1, std::min(o.max_chunks, (2048 + o.nkv * n_rs - 1) / (o.nkv * n_rs)));
-  // contexts of at most two pages: one kernel, a block per KV head and row
-  // slice folding its own pages.  The positions are the host's upper bound;
-  // a captured step is replayed at any length.
+  // short contexts: one kernel, a block per KV head and row slice folding its
+  // own pages.  Up to two pages for one row, one page for several (their
+  // second page costs more than the combine: the tiny model, 15 tokens at 69
+  // positions with 7 drafts, 1.09 ms so, 1.11 in two kernels throughout, 1.16
+  // with two pages for several rows too; 40 tokens from 20 positions 2.58,
+  // 2.77 and 2.73; Llama-2-7B widths, 4 layers, from 20 positions 9.22 against
+  // 9.40).  The positions are the host's upper bound; a captured step is
+  // replayed at any length.
   const int len = c->use_graphs ? o.max_ctx : (c->inflight.empty() ? c->seq_len : c->seq_ub) + pos_off + M;
-  at.short_ctx = len <= SHORT_PAGES * PAGE;
+  at.short_ctx = len <= (M == 1 ? 2 : 1) * PAGE;
   if (at.short_ctx) at.n_split = 1;
   at.max_chunks = o.max_chunks;
   at.part = c->S<float>(o.part);
