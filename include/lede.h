@@ -465,7 +465,8 @@ int lede_debug_inject_failure(lede_ctx* ctx, int32_t n_ops);
  * weights and KV read once, plus activations in and out. */
 enum {
   LEDE_K_LINEAR_VEC = 0,  /* one-row linear kernel, input row staged in LDS (draft path) */
-  LEDE_K_LINEAR_MFMA,     /* matrix-core linear kernel, input rows read from global memory (verify / prefill path) */
+  LEDE_K_LINEAR_MFMA,     /* matrix-core linear kernel, input rows read from global memory (verify path), and the
+                             many-row kernels of prefill */
   LEDE_K_ATTENTION,       /* paged attention partial + combine */
   LEDE_K_NORM,            /* RMSNorm rows */
   LEDE_K_QNET,            /* Q-network layers */
@@ -516,7 +517,8 @@ int lede_op_sample(const float* logits, int32_t V, float temperature, float u, i
  * capture, serving loops and harnesses that forbid hipMalloc): the draws of
  * lede_op_sample for n_rows rows at once, with no allocation.  Row r is the
  * device fp32 row logits + r * ld (V used entries, ld >= V), drawn with the
- * host uniform u[r] in [0, 1); tokens (host, [n_rows]) receives the draws.
+ * host uniform u[r] in [0, 1), in one launch; tokens (host, [n_rows]) receives
+ * the draws.
  * The draws' keys live in a library-owned static device array of 32 keys
  * (2 KiB per device, held until the process ends): n_rows above 32 is
  * LEDE_E_ARG, as are null pointers, V < 1, ld < V, a temperature that is not

@@ -20,6 +20,10 @@ __device__ __forceinline__ void top_insert(float (&t)[POLICY_TOPK], float x) {
 // at temperature 1, Q-values and the greedy action (ties: continue).
 //   C_k = log S - mean_{top k} (z - m),  H = log S - sum e (z - m) / S,
 // with m the max logit, e = exp(z - m), S = sum e.
+// Latency-bound: the host waits for the answer between draft tokens.  One pass,
+// since the head's argmax key already holds m; the row comes in shared 64-byte
+// pieces through LDS, and the Q-network's weights load before it.  15.3 us over
+// 32000 logits, 19.5 with a pass for m first and serial weight loads.
 __global__ __launch_bounds__(SB) void k_exit_policy(ExitPolicyArgs a) {
   __shared__ float red[SW];
   __shared__ float tops[SW][POLICY_TOPK];
