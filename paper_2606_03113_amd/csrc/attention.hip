@@ -207,7 +207,8 @@ __global__ __launch_bounds__(256) void k_attn_short(AttnArgs a) {
 // unconditional (a page index past the buffer is clamped to its last page,
 // and pages past the row's position are loaded but not folded), so each
 // group's 16 issue together, and before the sequence length arrives.
-template <int DT, int HD>
+// GROUPS: the partials are the groups' own, already folded (max_chunks of them).
+template <int DT, int HD, bool GROUPS = false>
 __global__ __launch_bounds__(HD * COMBINE_GROUPS) void k_attn_combine(AttnArgs a) {
   constexpr int B = 16;
   __shared__ float st[COMBINE_GROUPS][3][HD];
@@ -225,11 +226,17 @@ __global__ __launch_bounds__(HD * COMBINE_GROUPS) void k_attn_combine(AttnArgs a
       pa[u] = q[2 + i];
     }
   };
-  load(sg * B);
+  if (!GROUPS) load(sg * B);
   const int pos = *a.seq_len + a.pos_off + m;
   const int nc = pos / 64 + 1;
   float mx = -INFINITY, l = 0.f, acc = 0.f;
-  for (int j0 = sg * B; j0 < nc; j0 += S * B) {
+  if (GROUPS && sg * B < nc) {
+    const float* q = p + (size_t)sg * (HD + 2);
+    mx = q[0];
+    l = q[1];
+    acc = q[2 + i];
+  }
+  for (int j0 = sg * B; !GROUPS && j0 < nc; j0 += S * B) {
     if (j0 > sg * B) load(j0);
 #pragma unroll
     for (int u = 0; u < B; ++u)
@@ -476,7 +483,12 @@ __device__ __forceinline__ float pair_lanes(float v) {
 // about 2.7 us with one or two wavefronts per SIMD, and the same with pages
 // fetched two ahead): 2048 rows of the Llama-2-13B shape take 194 us a layer,
 // against 2180 for the two kernels 16 rows at a time; 97 rows 13 against 74.
-template <int HD>
+// SPLIT: few rows behind many pages leave CUs idle while the chain runs, so
+// their pages go to several blocks and the partials (1: of each page, 2: of
+// each group) through memory to k_attn_combine.  A pass of 97 tokens over two
+// layers of the Llama-3-8B shape (head included) takes 627 us behind 1024
+// positions, 668 unsplit; behind 2048 663 and 750, behind 8000 688 and 1194.
+template <int HD, int SPLIT>
 __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   constexpr int KS = HD / 32, NT = HD / 16;  // k-steps of the scores, output tiles
   constexpr int NW = 8, KT = 4 * KS;         // wavefronts, key tiles of a page
@@ -502,6 +514,8 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   const int nc_full = (pos0 + min(r0, R - 1) / G + 1) / 64;                            // those its first row sees whole,
   const int nc = (pos0 + min(rb * 16 * NW + 16 * NW - 1, R - 1) / G) / 64 + 1;        // of the block's
   const int S = min(COMBINE_GROUPS, (a.max_chunks + 15) / 16);  // groups of the combine kernel
+  const int j_first = SPLIT == 0 ? 0 : blockIdx.y * (SPLIT == 1 ? a.pages_per_block : 16);
+  if (SPLIT && j_first >= nc) return;
   uint4 qh[KS], ql[KS];
   {
     const float scale = rsqrtf((float)HD);
@@ -538,9 +552,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   // the page after j in the combine's order (-1: none): runs of 16 pages,
   // group sg taking runs sg, sg + S, ...
   auto next = [&](int j) {
+    if (SPLIT == 1) return j + 1 < min(nc, j_first + a.pages_per_block) ? j + 1 : -1;
     if ((j & 15) != 15 && j + 1 < nc) return j + 1;
     const int run = j >> 4;
     if ((run + S) * 16 < nc) return (run + S) * 16;
+    if (SPLIT == 2) return -1;
     const int sg = run % S + 1;
     return sg < S && sg * 16 < nc ? sg * 16 : -1;
   };
@@ -550,9 +566,10 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   for (int d = 0; d < NT; ++d) ga[d] = ta[d] = f32x4{0.f, 0.f, 0.f, 0.f};
   uint32_t* ph_s = pb + (w * 2) * 16 * VS;
   uint32_t* pl_s = ph_s + 16 * VS;
+  float* part = SPLIT ? a.part + ((size_t)m_row * a.nq + head) * a.n_parts * (HD + 2) : nullptr;
   int buf = 0;
-  fetch(0, 0);
-  for (int j = 0; j >= 0; buf ^= 1) {
+  fetch(j_first, 0);
+  for (int j = j_first; j >= 0; buf ^= 1) {
     const int nj = next(j);
     if (v_on) {
       const uint32_t e0[4] = {v0.x, v0.y, v0.z, v0.w}, e1[4] = {v1.x, v1.y, v1.z, v1.w};
@@ -653,6 +670,19 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
 #pragma unroll
           for (int d = 0; d < 4; ++d) oc[d] = mfma_tile<1>(vt[d], po[ks], oc[d]);
         }
+        if (SPLIT == 1) {
+          if (row_ok && in) {
+            float* q = part + (size_t)j * (HD + 2);
+            if (d0 == 0 && lg == 0) *(float2*)q = make_float2(mx, pl);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+              float2* qd = (float2*)(q + 2 + 16 * (d0 + d) + 4 * lg);
+              qd[0] = make_float2(oc[d][0], oc[d][1]);
+              qd[1] = make_float2(oc[d][2], oc[d][3]);
+            }
+          }
+          continue;
+        }
 #pragma unroll
         for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -660,7 +690,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
       }
     }
     const int sg = (j >> 4) % S;
-    if (nj < 0 || (nj >> 4) % S != sg) {  // the group ends: fold it into the total
+    if (SPLIT == 0 && (nj < 0 || (nj >> 4) % S != sg)) {  // the group ends: fold it into the total
       const bool in = 16 * sg < nc_row;
       const float nm = fmaxf(tm, gm);
       const float so = tm == -INFINITY ? 0.f : __expf(tm - nm), sn = __expf(gm - nm);
@@ -680,7 +710,17 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
     }
     j = nj;
   }
-  if (row_ok) {
+  if (SPLIT == 2 && row_ok && j_first < nc_row) {
+    float* q = part + (size_t)blockIdx.y * (HD + 2);
+    if (lg == 0) *(float2*)q = make_float2(gm, gl);
+#pragma unroll
+    for (int d = 0; d < NT; ++d) {
+      float2* qd = (float2*)(q + 2 + 16 * d + 4 * lg);
+      qd[0] = make_float2(ga[d][0], ga[d][1]);
+      qd[1] = make_float2(ga[d][2], ga[d][3]);
+    }
+  }
+  if (SPLIT == 0 && row_ok) {
 #pragma unroll
     for (int d = 0; d < NT; ++d)
       store4<1>((uint8_t*)a.out + tiled_row_off<1>(m_row, head * HD + 16 * d + 4 * lg, a.KT_tiled), 0,
@@ -688,15 +728,65 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   }
 }
 
+// How a prefill pass's pages are split, at n_pos positions in all: the pass's
+// time is the chain of a block's pages, 2.7 us each, and, where they are split,
+// 4 us for a second launch and the partials' way through memory at 4 TB/s.
+// Partials of every page, split so that no CU gets two blocks, or of the
+// combine's groups; part_bytes bounds them.  The estimate has to win by a
+// tenth: at 64 to 200 cached positions (three to five pages) both ways take
+// the same time within 0.5 %.
+void plan_attention_wide(AttnArgs& a, int n_pos, size_t part_bytes) {
+  const int rows = a.M * (a.nq / a.nkv), blocks = a.nkv * ((rows + 127) / 128);
+  const int P = (n_pos + 63) / 64, S = (a.max_chunks + 15) / 16 < COMBINE_GROUPS ? (a.max_chunks + 15) / 16 : COMBINE_GROUPS;
+  const int used = (P + 15) / 16 < S ? (P + 15) / 16 : S;  // groups that have pages
+  const double part_mb = (double)a.M * a.nq * (a.hd + 2) * 4 * 1e-6;  // of one partial
+  double best = 2.7 * P * ((blocks + 255) / 256);
+  a.wide_split = 0;
+  auto consider = [&](int split, int n_blocks, int n_parts, int chain, int pages) {
+    const double t = 1.1 * (2.7 * chain * ((blocks * n_blocks + 255) / 256) + 4 + 2 * part_mb * n_parts / 4);
+    if (part_mb * 1e6 * n_parts > (double)part_bytes || t >= best) return;
+    best = t;
+    a.wide_split = split;
+    a.n_parts = n_parts;
+    a.pages_per_block = pages;
+    a.n_split = n_blocks;
+  };
+  const int per = 256 / blocks;  // blocks that a row block's pages may go to
+  if (per >= 2) {
+    const int pages = (P + per - 1) / per;
+    consider(1, (P + pages - 1) / pages, P, pages, pages);
+  }
+  if (used >= 2) consider(2, used, used, ((P + 15) / 16 + S - 1) / S * 16, 0);
+}
+
 hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s) {
   const int rows = a.M * (a.nq / a.nkv), n_rb = (rows + 127) / 128;
-  const dim3 grid(8 * ((a.nkv + 7) / 8) * n_rb);
+  const dim3 grid(8 * ((a.nkv + 7) / 8) * n_rb, a.wide_split ? a.n_split : 1);
   const int lds = 2 * (a.hd / 8) * 1024 + (2 * a.hd + 8 * 2 * 16) * 36 * 4;
-  const void* f = a.hd == 128 ? (const void*)k_attn_wide<128> : (const void*)k_attn_wide<64>;
+  static const void* const kernels[2][3] = {
+      {(const void*)k_attn_wide<64, 0>, (const void*)k_attn_wide<64, 1>, (const void*)k_attn_wide<64, 2>},
+      {(const void*)k_attn_wide<128, 0>, (const void*)k_attn_wide<128, 1>, (const void*)k_attn_wide<128, 2>}};
+  const void* f = kernels[a.hd == 128][a.wide_split];
   hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
   void* args[] = {(void*)&a};
-  return hipLaunchKernel(f, grid, dim3(512), args, lds, s);
+  e = hipLaunchKernel(f, grid, dim3(512), args, lds, s);
+  if (e != hipSuccess || !a.wide_split) return e;
+  // the combine's groups: those that have pages (page j belongs to group
+  // j / 16 modulo the groups of max_ctx, so a group without pages may be left out)
+  const int S = (a.max_chunks + 15) / 16 < COMBINE_GROUPS ? (a.max_chunks + 15) / 16 : COMBINE_GROUPS;
+  AttnArgs b = a;
+  b.max_chunks = a.n_parts;
+  const int runs = a.wide_split == 1 ? (a.n_parts + 15) / 16 : a.n_parts, groups = runs < S ? runs : S;
+  const dim3 cgrid(a.M * a.nq), cblock(a.hd * groups);
+  if (a.wide_split == 1) {
+    if (a.hd == 128) hipLaunchKernelGGL((k_attn_combine<1, 128>), cgrid, cblock, 0, s, b);
+    else hipLaunchKernelGGL((k_attn_combine<1, 64>), cgrid, cblock, 0, s, b);
+  } else {
+    if (a.hd == 128) hipLaunchKernelGGL((k_attn_combine<1, 128, true>), cgrid, cblock, 0, s, b);
+    else hipLaunchKernelGGL((k_attn_combine<1, 64, true>), cgrid, cblock, 0, s, b);
+  }
+  return hipGetLastError();
 }
 
 template <int DT, int HD>

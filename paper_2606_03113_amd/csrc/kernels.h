@@ -31,9 +31,12 @@ struct AttnArgs {
   int rows_per_block;              // <= 16 query rows (m, head-in-group) per block
   int short_ctx;                   // at most 16 pages, all taken by one block per (kv head, row slice), which folds them itself (n_split 1)
   int max_chunks;
-  float* part;                     // [M][nq][max_chunks][hd + 2]
+  float* part;                     // [M][nq][max_chunks][hd + 2] (wide_split: [M][nq][n_parts][hd + 2])
   void* out; int ldo;              // combine output [M][nq*hd], model dtype
   int KT_tiled;                    // > 0: tiled output rows (wide.h) of this many tiles
+  // k_attn_wide: 0 a block walks all of a row's pages; 1 pages_per_block of
+  // them, partials of each page; 2 the pages of one combine group, one partial
+  int wide_split, pages_per_block, n_parts;
   int mfma;                        // bf16: partials on the matrix cores (rows of verify, prefill, AR)
 };
 
@@ -153,6 +156,7 @@ hipError_t launch_norm(int dtype, const NormArgs& a, hipStream_t s);
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s);
 // Any number of rows (bf16, tiled output): the bits of launch_attention's
 // matrix-core path.
+void plan_attention_wide(AttnArgs& a, int n_pos, size_t part_bytes);
 hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s);
 hipError_t launch_qnet_out(const QnetOutArgs& a, hipStream_t s);
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t s);

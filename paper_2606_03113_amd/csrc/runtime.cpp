@@ -738,8 +738,13 @@ int run_wide(lede_ctx* c, int M, const int32_t* tokens, int pos_off, bool head, 
       AttnArgs at = attn_args(c, j, M, false, pos_off);
       at.q = c->S<float>(o.wq);
       at.out = c->S<uint8_t>(o.wattn); at.KT_tiled = KTq;
-      const double n_pos = (double)c->seq_len + pos_off + M;
-      LAUNCH(LEDE_K_ATTENTION, n_pos * o.kvd * 2.0 * o.es + 2.0 * M * o.qd * 4, launch_attention_wide(at, s));
+      const int n_pos = c->seq_len + pos_off + M;
+      // partials, where there are any, lie in the activations' rows, which
+      // hold nothing here (the zeros past F in a last tile that is not full
+      // have to stay: no partials then)
+      at.part = c->S<float>(o.wact);
+      plan_attention_wide(at, n_pos, (size_t)KTf * TILE_BYTES == (size_t)o.F * 16 * o.es ? (size_t)o.wide_rows / 16 * KTf * TILE_BYTES : 0);
+      LAUNCH(LEDE_K_ATTENTION, (double)n_pos * o.kvd * 2.0 * o.es + 2.0 * M * o.qd * 4, launch_attention_wide(at, s));
     } else {
       for (int r = 0; r < M; r += MROWS) {
         const int m = std::min(MROWS, M - r);

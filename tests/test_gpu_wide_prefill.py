@@ -22,6 +22,7 @@ GQA_128_F32 = shrink(TINY, name="f32-gqa-hd128", n_layers=2, d_model=512, n_head
                      ffn_dim=704, vocab=1024, dtype="f32", qnet_hidden=32, exits=(1, 2))
 GQA_8 = shrink(TINY, name="bf16-gqa8-hd128", n_layers=1, d_model=1024, n_heads=16, n_kv_heads=2, head_dim=128,
                ffn_dim=1376, vocab=1024, dtype="bf16", qnet_hidden=32, exits=(1,))
+GQA_64_F = shrink(GQA_64, name="bf16-gqa-hd64-f1024", ffn_dim=1024)
 MODELS = [TINY, BF16_64, BF16_128, GQA_64, GQA_128_F32, GQA_8]
 # (tokens already cached, new tokens): one past a group, edges of row tiles and
 # pages, ragged ends, several page groups behind the rows
@@ -74,16 +75,29 @@ def test_prefill_of_several_passes(model):
     _check(model, 2400, 40, 2201)
 
 
-def test_prefill_past_128_pages():
-    """Contexts longer than one round of the page combine's eight groups."""
-    say("wide prefill, 130 pages")
-    _check(shrink(GQA_64, n_layers=1, exits=(1,)), 8400, 8190, 130)
+@pytest.mark.parametrize("model", [GQA_64, GQA_64_F], ids=lambda m: m.name)
+def test_prefill_past_128_pages(model):
+    """Contexts longer than one round of the page combine's eight groups,
+    walked by one block per row block, and split over the groups."""
+    say("wide prefill, 130 pages", model.name)
+    _check(shrink(model, n_layers=1, exits=(1,)), 8400, 8190, 130)
 
 
-@pytest.mark.parametrize("n", [40, 200])
-def test_prefill_at_full_width(n):
-    """One layer at the Llama-2-7B widths."""
+@pytest.mark.parametrize("model,ctx,n", [(GQA_8, 1300, 30), (GQA_8, 2130, 130), (BF16_128, 1980, 17), (GQA_64_F, 1500, 260),
+                                         (GQA_64, 1500, 130)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_prefill_behind_many_pages(model, ctx, n):
+    """Few rows behind many pages: the pages are split over blocks, with
+    partials of pages (first and third) or of the combine's groups (second and
+    fourth); not where the feed-forward width leaves a tile partly empty (last)."""
+    say("wide prefill, many pages", model.name, ctx, n)
+    _check(model, 2400, ctx, n)
+
+
+@pytest.mark.parametrize("ctx,n", [(33, 40), (33, 200), (1000, 40)])
+def test_prefill_at_full_width(ctx, n):
+    """One layer at the Llama-2-7B widths (the last with blocks of three pages)."""
     from lede_inputs.configs import WORKLOADS
     m = shrink(WORKLOADS["llama2-7b"].model, n_layers=1, exits=(1,))
-    say("wide prefill, 7B widths", n)
-    _check(m, 512, 33, n)
+    say("wide prefill, 7B widths", ctx, n)
+    _check(m, 512 if ctx < 512 else 1100, ctx, n)
