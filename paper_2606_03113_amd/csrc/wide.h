@@ -21,6 +21,18 @@ __host__ __device__ inline size_t tiled_row_off(int m, int k, int KT) {
          (size_t)(k % TL::EPL) * TL::ES;
 }
 
+// The order in which the many-row kernels that stage their operands walk the
+// K tiles: class 0, 8, 1, 9, ... 7, 15 (class c: tiles c, c + 16, ...; classes
+// past the last tile are empty).  After the last tile t stays past the end:
+// the walk stops at class 15, whatever classes are empty.
+struct KWalk {
+  int t = 0, base = 0;  // the tile, and its class
+  __host__ __device__ inline void next(int KT) {
+    t += 16;
+    while (t >= KT && base != 15) t = base = base < 8 ? base + 8 : base - 7;
+  }
+};
+
 constexpr int WIDE_ROW_PAD = 128;  // row buffers hold a multiple of this many rows
 
 struct WideArgs {

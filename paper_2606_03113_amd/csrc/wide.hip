@@ -266,15 +266,6 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_wide_lds(WideArgs a) {
     src[i] = (u < GN ? a.w + (size_t)min(g0 + u, a.n_groups - 1) * KT * TILE_BYTES
                      : a.x + (size_t)min(r0 + u - GN, MG - 1) * KT * TILE_BYTES) + lane * 16;
   }
-  // the K walk: tile t of class base; next() steps it
-  auto next = [&](int& t, int& base) {
-    t += 16;
-    if (t >= KT) {
-      do base = base < 8 ? base + 8 : base - 7;
-      while (base >= KT && base < 16);
-      t = base;
-    }
-  };
   auto stage = [&](int slot, int t) {
 #pragma unroll
     for (int i = 0; i < PER; ++i)
@@ -282,11 +273,11 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_wide_lds(WideArgs a) {
                                        (__attribute__((address_space(3))) void*)(smem + (slot * TILES + min(wave * PER + i, TILES - 1)) * TILE_BYTES),
                                        16, 0, 0);
   };
-  int lt = 0, lbase = 0;  // the walk of the copies, D tiles ahead
+  KWalk cw;  // the walk of the copies, D tiles ahead
   for (int i = 0; i < D; ++i)
     if (i < KT) {
-      stage(i, lt);
-      next(lt, lbase);
+      stage(i, cw.t);
+      cw.next(KT);
     }
   const int wn = wave % WN, wm = wave / WN;
   const uint32_t la = wn * TN * TILE_BYTES + lane * 16, lb = (GN + wm * TM) * TILE_BYTES + lane * 16;
@@ -311,8 +302,8 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_wide_lds(WideArgs a) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) xv[i] = xnext[i];
     if (st + D < KT) {
-      stage(PF == TN ? slot : slot == 0 ? S - 1 : slot - 1, lt);
-      next(lt, lbase);
+      stage(PF == TN ? slot : slot == 0 ? S - 1 : slot - 1, cw.t);
+      cw.next(KT);
     }
     slot = slot == S - 1 ? 0 : slot + 1;
     read(slot);

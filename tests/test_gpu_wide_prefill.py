@@ -101,3 +101,19 @@ def test_prefill_at_full_width(ctx, n):
     m = shrink(WORKLOADS["llama2-7b"].model, n_layers=1, exits=(1,))
     say("wide prefill, 7B widths", ctx, n)
     _check(m, 512 if ctx < 512 else 1100, ctx, n)
+
+
+# widths of a single K tile (32 bf16 or 16 fp32 columns), with enough rows and
+# columns for the staged kernel: gate-up and QKV, then down, with the tile full
+# and partly filled
+K1 = dict(n_layers=2, n_heads=2, n_kv_heads=1, head_dim=64, vocab=512, qnet_hidden=32, exits=(1, 2))
+K1_MODELS = [(shrink(TINY, name="bf16-d32", d_model=32, ffn_dim=1376, dtype="bf16", **K1), 600),
+             (shrink(TINY, name="bf16-f32", d_model=4096, ffn_dim=32, dtype="bf16", **K1), 420),
+             (shrink(TINY, name="bf16-f8", d_model=4096, ffn_dim=8, dtype="bf16", **K1), 420),
+             (shrink(TINY, name="f32-f16", d_model=4096, ffn_dim=16, dtype="f32", **K1), 700)]
+
+
+@pytest.mark.parametrize("model,n", K1_MODELS, ids=lambda v: getattr(v, "name", v))
+def test_prefill_of_one_k_tile(model, n):
+    say("wide prefill, one K tile", model.name, n)
+    _check(model, 768, 0, n)
