@@ -2,6 +2,8 @@
 #include "device.h"
 #include "wide.h"
 
+#include <float.h>
+
 namespace lede {
 
 // ---- attention over the paged KV cache --------------------------------------
@@ -616,9 +618,10 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
       }
       mx = pair_lanes<32, true>(pair_lanes<16, true>(mx));
       // a row that ends before this page takes no part in it: weights of 0,
-      // folded with factors that leave its state as it is
+      // folded with factors that leave its state as it is (weights of 0 also
+      // where every score overflowed to -infinity)
       const bool in = j < nc_row;
-      const float ms = in ? mx : 0.f;
+      const float ms = in ? fmaxf(mx, -FLT_MAX) : 0.f;
       float pl = 0.f;
 #pragma unroll
       for (int tg = 0; tg < 4; ++tg) {

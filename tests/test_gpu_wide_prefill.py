@@ -117,3 +117,41 @@ K1_MODELS = [(shrink(TINY, name="bf16-d32", d_model=32, ffn_dim=1376, dtype="bf1
 def test_prefill_of_one_k_tile(model, n):
     say("wide prefill, one K tile", model.name, n)
     _check(model, 768, 0, n)
+
+
+@pytest.mark.parametrize("ffn", [256, 264], ids=["split", "unsplit"])
+def test_page_of_overflowed_scores(ffn):
+    """Cached keys so large that every score of a page overflows to -inf: the
+    page has no weight, as in the 16-row kernels.  Every query has a large
+    element in a slowly rotating dimension, in which the second page's keys
+    hold -3e38; with the feed-forward width a multiple of a tile the pages are
+    split over blocks."""
+    from paper_2606_03113_amd import Engine
+    hd, ctx, n = 64, 128, 40
+    m = shrink(TINY, name="overflow", n_layers=2, n_heads=2, n_kv_heads=1, head_dim=hd, ffn_dim=ffn, dtype="bf16",
+               qnet_hidden=32, exits=(1, 2))
+    bf16 = lambda x: int(np.float32(x).view(np.uint32) >> 16)  # noqa: E731
+    w = li.weights(m)
+    w["embed"][:, 0] = bf16(0.08)
+    for layer in w["layers"]:
+        layer["wq"][hd // 2 - 1::hd, 0] = bf16(60.0)
+    toks = li.uniform_int(1, 20, ctx + n, 0, m.vocab - 1)
+    got = []
+    for step in (n, 16):
+        say("wide prefill, overflowed scores", ffn, step)
+        eng = Engine(m, max_ctx=256, k_max=8)
+        eng.kv.zero_()
+        eng.load_weights(w, li.qnet_weights(m))
+        eng.lede_set_options(0, 1)
+        eng.lede_prefill(toks[:ctx])
+        page = eng.lede_get_kv_state()[2][1]
+        keys = eng.kv[:eng.region_bytes[1] // 2].view(torch.int16)[:2 * eng.cfg.n_pages * 64 * hd].view(2, -1, 64, hd)
+        keys[0, page] = 0
+        keys[0, page, :, hd // 2 - 1] = bf16(-3e38) - (1 << 16)
+        torch.cuda.synchronize()
+        for i in range(ctx, ctx + n, step):
+            eng.lede_prefill(toks[i:min(ctx + n, i + step)])
+        got.append(_state(eng))
+        eng.close()
+    assert np.isfinite(got[1][4]).all()
+    assert np.array_equal(got[0][4], got[1][4]) and np.array_equal(got[0][3], got[1][3])
