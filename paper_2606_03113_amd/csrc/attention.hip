@@ -4,6 +4,8 @@
 
 #include <float.h>
 
+#include <type_traits>
+
 namespace lede {
 
 // ---- attention over the paged KV cache --------------------------------------
@@ -507,12 +509,13 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   const int jx = blockIdx.x >> 3;
   const int kvh = (jx / n_rb) * 8 + (blockIdx.x & 7), rb = n_rb - 1 - jx % n_rb;
   if (kvh >= a.nkv) return;
-  const int pos0 = *a.seq_len + a.pos_off, pmax = pos0 + a.M - 1;
+  const int pos0 = *a.seq_len + a.pos_off;
   const int r0 = rb * 16 * NW + 16 * w, rr = min(r0 + lr, R - 1);
   const bool row_ok = r0 + lr < R;
   const int m_row = rr / G, head = kvh * G + rr % G, row_pos = pos0 + m_row;
   const int nc_row = row_pos / 64 + 1;                                                // pages of this lane's row,
-  const int nc_wave = r0 < R ? (pos0 + min(r0 + 15, R - 1) / G) / 64 + 1 : 0;         // of its wavefront's,
+  const int last_wave = pos0 + min(r0 + 15, R - 1) / G;                               // (its wavefront's last position)
+  const int nc_wave = r0 < R ? last_wave / 64 + 1 : 0;                                // of its wavefront's,
   const int nc_full = (pos0 + min(r0, R - 1) / G + 1) / 64;                            // those its first row sees whole,
   const int nc = (pos0 + min(rb * 16 * NW + 16 * NW - 1, R - 1) / G) / 64 + 1;        // of the block's
   const int S = min(COMBINE_GROUPS, (a.max_chunks + 15) / 16);  // groups of the combine kernel
@@ -576,12 +579,10 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
     if (v_on) {
       const uint32_t e0[4] = {v0.x, v0.y, v0.z, v0.w}, e1[4] = {v1.x, v1.y, v1.z, v1.w};
       uint32_t* dst = vb + (buf * HD + 8 * dg) * VS + tp;
-      // slots past the last row's position hold no value yet
-      const uint32_t vm = (j * 64 + 2 * tp <= pmax ? 0xFFFFu : 0u) | (j * 64 + 2 * tp + 1 <= pmax ? 0xFFFF0000u : 0u);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        dst[(2 * e) * VS] = __builtin_amdgcn_perm(e1[e], e0[e], 0x05040100u) & vm;
-        dst[(2 * e + 1) * VS] = __builtin_amdgcn_perm(e1[e], e0[e], 0x07060302u) & vm;
+        dst[(2 * e) * VS] = __builtin_amdgcn_perm(e1[e], e0[e], 0x05040100u);
+        dst[(2 * e + 1) * VS] = __builtin_amdgcn_perm(e1[e], e0[e], 0x07060302u);
       }
     }
     // page j is in LDS, and page j - 1 no longer read
@@ -657,40 +658,61 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
       const float so = !in ? 1.f : gm == -INFINITY ? 0.f : __expf(gm - nm), sn = in ? __expf(mx - nm) : 0.f;
       gl = fmaf(pl, sn, gl * so);
       gm = nm;
+      auto weigh = [&](auto masked) {
+        // slots past the wavefront's last position hold no value yet, or
+        // another wavefront's, which a weight of 0 would not keep out if it
+        // is infinite
+        uint32_t vm[2][4];
+        if (masked) {
 #pragma unroll
-      for (int d0 = 0; d0 < NT; d0 += 4) {
-        f32x4 oc[4];
+          for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int d = 0; d < 4; ++d) oc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          uint4 vt[4];
-#pragma unroll
-          for (int d = 0; d < 4; ++d)
-            vt[d] = lds_ld16((const uint8_t*)&vb[(buf * HD + 16 * (d0 + d) + lr) * VS + 16 * ks + 4 * lg]);
-#pragma unroll
-          for (int d = 0; d < 4; ++d) oc[d] = mfma_tile<1>(vt[d], ph[ks], oc[d]);
-#pragma unroll
-          for (int d = 0; d < 4; ++d) oc[d] = mfma_tile<1>(vt[d], po[ks], oc[d]);
+            for (int i = 0; i < 4; ++i) {
+              const int t = j * 64 + 32 * ks + 8 * lg + 2 * i;
+              vm[ks][i] = t < last_wave ? ~0u : t == last_wave ? 0xFFFFu : 0u;
+            }
         }
-        if (SPLIT == 1) {
-          if (row_ok && in) {
-            float* q = part + (size_t)j * (HD + 2);
-            if (d0 == 0 && lg == 0) *(float2*)q = make_float2(mx, pl);
+#pragma unroll
+        for (int d0 = 0; d0 < NT; d0 += 4) {
+          f32x4 oc[4];
+#pragma unroll
+          for (int d = 0; d < 4; ++d) oc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) {
+            uint4 vt[4];
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-              float2* qd = (float2*)(q + 2 + 16 * (d0 + d) + 4 * lg);
-              qd[0] = make_float2(oc[d][0], oc[d][1]);
-              qd[1] = make_float2(oc[d][2], oc[d][3]);
+              vt[d] = lds_ld16((const uint8_t*)&vb[(buf * HD + 16 * (d0 + d) + lr) * VS + 16 * ks + 4 * lg]);
+              if (masked) {
+                vt[d].x &= vm[ks][0]; vt[d].y &= vm[ks][1]; vt[d].z &= vm[ks][2]; vt[d].w &= vm[ks][3];
+              }
             }
+#pragma unroll
+            for (int d = 0; d < 4; ++d) oc[d] = mfma_tile<1>(vt[d], ph[ks], oc[d]);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) oc[d] = mfma_tile<1>(vt[d], po[ks], oc[d]);
           }
-          continue;
+          if (SPLIT == 1) {
+            if (row_ok && in) {
+              float* q = part + (size_t)j * (HD + 2);
+              if (d0 == 0 && lg == 0) *(float2*)q = make_float2(mx, pl);
+#pragma unroll
+              for (int d = 0; d < 4; ++d) {
+                float2* qd = (float2*)(q + 2 + 16 * (d0 + d) + 4 * lg);
+                qd[0] = make_float2(oc[d][0], oc[d][1]);
+                qd[1] = make_float2(oc[d][2], oc[d][3]);
+              }
+            }
+            continue;
+          }
+#pragma unroll
+          for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ga[d0 + d][i] = fmaf(oc[d][i], sn, ga[d0 + d][i] * so);
         }
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) ga[d0 + d][i] = fmaf(oc[d][i], sn, ga[d0 + d][i] * so);
-      }
+      };
+      if (ends) weigh(std::true_type{});
+      else weigh(std::false_type{});
     }
     const int sg = (j >> 4) % S;
     if (SPLIT == 0 && (nj < 0 || (nj >> 4) % S != sg)) {  // the group ends: fold it into the total
