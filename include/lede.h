@@ -140,6 +140,10 @@ typedef struct {
 
 /* Bytes of the three device regions the caller allocates for `cfg`:
  * the weight arena (repacked weights), the KV pool and the workspace.
+ * The end of the workspace holds the rows of lede_prefill's passes, for
+ * R = min(2048, max_ctx rounded up to a multiple of 128) rows, about
+ * R (d_model (4.25 + e) + q_dim (4 + e) + ffn_dim e) bytes with e bytes per
+ * element (65 of 74 MB at the Llama-2-7B widths and 777 positions).
  * Returns LEDE_E_UNSUPPORTED for shapes the kernels do not handle
  * (head_dim not 64/128, d_model or q_dim not a multiple of 32, d_model above
  * 8192, ffn_dim not a multiple of 8, page_size != 64, k_max > 15, ...). */
@@ -147,8 +151,12 @@ int lede_region_bytes(const lede_config* cfg, size_t* weight_bytes, size_t* kv_b
                       size_t* workspace_bytes);
 
 /* Create a context on the current device over caller-owned regions of at
- * least the sizes above (256-byte aligned).  Uploads the RoPE table to the
- * workspace (synchronous).  The page free list starts as 0..n_pages-1. */
+ * least the sizes above (256-byte aligned).  A smaller workspace holds fewer
+ * rows of a prefill pass (multiples of 128; in the end none: prompts then go
+ * through 16-row passes, with the same bits, slower); LEDE_E_ARG when it is
+ * too small for that as well, which is the size above less those rows.
+ * Uploads the RoPE table to the workspace (synchronous).  The page free list
+ * starts as 0..n_pages-1. */
 int lede_create(const lede_config* cfg, void* weight_arena, size_t weight_bytes, void* kv_pool,
                 size_t kv_bytes, void* workspace, size_t workspace_bytes, lede_ctx** out);
 
@@ -204,10 +212,11 @@ int lede_set_verify_reuse(lede_ctx* ctx, int32_t enable);
 /* Prefill (the paper does not describe it; decoding in Section 4.1 starts
  * from a prompt at batch 1): append n prompt tokens (host int32, each in
  * [0, vocab)) at positions seq_len .. seq_len+n-1 through all L layers,
- * writing their K/V, in passes of up to 2048 rows whose results are bit for
- * bit those of the verify kernels; the full model's
- * argmax at the last row becomes the pending token and is returned in
- * *next_token (host), and its -log max p enters the confidence trace.
+ * writing their K/V, in passes of up to 2048 rows (fewer in a smaller
+ * workspace) whose results are bit for bit those of the verify kernels; the
+ * full model's argmax at the last row becomes the pending token and is
+ * returned in *next_token (host), and its -log max p enters the confidence
+ * trace.
  * Valid when no draft is outstanding (LEDE_E_STATE); LEDE_E_ARG on a null
  * pointer, n < 1 or a token out of range; LEDE_E_CTX_OVERFLOW /
  * LEDE_E_KV_FULL when the positions do not fit.  Synchronises. */

@@ -42,10 +42,10 @@ struct Layout {
   // workspace offsets
   size_t h, xn, ss, q, attn_out, act, part, logits, gstats, dkeys, vkeys, qs, qhid, qv, seq_len, btab, prompt,
       record, rope, unif, dstats, trace, trace_state, trace_bak, pol_out, wsbytes;
-  // rows of a many-row prefill pass (wide_rows of them; the rest as h .. act, row inputs tiled)
-  int wide_rows;
   size_t rstats;  // [MROWS][2] statistics of logits rows (sampled acceptance, confidence trace)
-  size_t wh, wxn, wss, winv, wq, wattn, wact;
+  // rows of a many-row prefill pass, at the workspace's end (wide_rows of them; the rest as h .. act, row inputs tiled)
+  int wide_rows;
+  size_t wide0, wh, wxn, wss, winv, wq, wattn, wact;
   size_t kvbytes, kv_half;
 };
 
@@ -74,6 +74,22 @@ const char* check_config(const lede_config* c) {
       if (c->lengths[i] < 1 || c->lengths[i] > 16) return "lengths must be in 1..16";
   }
   return nullptr;
+}
+
+// The buffers of many-row prefill passes, for `rows` rows (a multiple of
+// WIDE_ROW_PAD, or 0: none), and the workspace's size.
+void place_wide(Layout& o, int rows) {
+  size_t off = o.wide0;
+  auto take = [&](size_t bytes) { size_t r = off; off += align256(bytes); return r; };
+  const size_t wr = o.wide_rows = rows;
+  o.wh = take(wr * o.d * 4);
+  o.wxn = take(wr / 16 * k_tiles(o.dt, o.d) * TILE_BYTES);
+  o.wss = take(wr * (o.d / 16) * 4);
+  o.winv = take(wr * 4);
+  o.wq = take(wr * o.qd * 4);
+  o.wattn = take(wr / 16 * k_tiles(o.dt, o.qd) * TILE_BYTES);
+  o.wact = take(wr / 16 * k_tiles(o.dt, o.F) * TILE_BYTES);
+  o.wsbytes = off;
 }
 
 Layout make_layout(const lede_config* c) {
@@ -135,22 +151,14 @@ Layout make_layout(const lede_config* c) {
   o.record = take(RECORD_INTS * 4);
   o.rope = take((size_t)o.max_ctx * (o.hd / 2) * 8);
   o.unif = take(UNIF_FLOATS * 4);
-  o.dstats = take(2 * SAMPLE_SLOTS * 4);
+  o.dstats = take((2 * SAMPLE_SLOTS + 2 * MROWS) * 4);
+  o.rstats = o.dstats + 2 * SAMPLE_SLOTS * 4;
   o.trace = take(POLICY_TRACE * 4);
   o.trace_state = take(4 * 4);
   o.trace_bak = take((POLICY_TRACE + 2) * 4);
   o.pol_out = take((size_t)(c->n_exits + POLICY_MAX_DRAFT) * POLICY_LOG * 4);
-  o.rstats = take(MROWS * 2 * 4);
-  o.wide_rows = std::min(WIDE_ROWS, (o.max_ctx + WIDE_ROW_PAD - 1) / WIDE_ROW_PAD * WIDE_ROW_PAD);
-  const size_t wr = o.wide_rows;
-  o.wh = take(wr * o.d * 4);
-  o.wxn = take(wr / 16 * k_tiles(o.dt, o.d) * TILE_BYTES);
-  o.wss = take(wr * (o.d / 16) * 4);
-  o.winv = take(wr * 4);
-  o.wq = take(wr * o.qd * 4);
-  o.wattn = take(wr / 16 * k_tiles(o.dt, o.qd) * TILE_BYTES);
-  o.wact = take(wr / 16 * k_tiles(o.dt, o.F) * TILE_BYTES);
-  o.wsbytes = off;
+  o.wide0 = off;
+  place_wide(o, std::min(WIDE_ROWS, (o.max_ctx + WIDE_ROW_PAD - 1) / WIDE_ROW_PAD * WIDE_ROW_PAD));
 
   o.kv_half = align256((size_t)o.L * o.n_pages * o.nkv * PAGE * o.hd * o.es);
   o.kvbytes = 2 * o.kv_half;
@@ -1054,7 +1062,8 @@ int lede_create(const lede_config* cfg, void* warena, size_t wbytes, void* kv, s
   if (!cfg || !warena || !kv || !ws) return LEDE_E_ARG;
   if (check_config(cfg)) return LEDE_E_UNSUPPORTED;
   Layout o = make_layout(cfg);
-  if (wbytes < o.wbytes || kvbytes < o.kvbytes || wsbytes < o.wsbytes) return LEDE_E_ARG;
+  if (wbytes < o.wbytes || kvbytes < o.kvbytes || wsbytes < o.wide0) return LEDE_E_ARG;
+  while (wsbytes < o.wsbytes) place_wide(o, o.wide_rows - WIDE_ROW_PAD);  // as many rows as fit
   if (((uintptr_t)warena | (uintptr_t)kv | (uintptr_t)ws) & 255) return LEDE_E_ARG;
   lede_ctx* c = new lede_ctx();
   c->cfg = *cfg;
@@ -1269,7 +1278,8 @@ static int prefill_impl(lede_ctx* c, const int32_t* tokens, int32_t n, hipStream
   HIP_CHECK(c, hipMemcpyAsync(pd, tokens, (size_t)n * 4, hipMemcpyHostToDevice, s));
   uint64_t* vk = c->S<uint64_t>(c->lo.vkeys);
   // passes of about equal size, whole row groups except the last
-  const int passes = (n + c->lo.wide_rows - 1) / c->lo.wide_rows;
+  const int most = std::max(c->lo.wide_rows, MROWS);
+  const int passes = (n + most - 1) / most;
   const int rows = ((n + passes - 1) / passes + MROWS - 1) / MROWS * MROWS;
   for (int off = 0; off < n; off += rows) {
     const int M = std::min(rows, n - off);

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import lede_inputs as li
 from lede_inputs.configs import WORKLOADS, TINY, shrink
@@ -230,3 +231,22 @@ def test_dqn_null_and_region_checks(lib):
     assert lib.lede_dqn_read(None, 0, None, 0, None, None) == -1
     assert lib.lede_dqn_last_error(None) == b"null handle"
     lib.lede_dqn_destroy(None)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="passes addresses that are never read without a GPU")
+@pytest.mark.parametrize("dtype,d,hd,ffn,layers,bytes_min", [("f32", 256, 64, 688, 4, 500992),
+                                                             ("bf16", 512, 128, 1376, 3, 1207552)])
+def test_workspace_without_rows_of_a_prefill_pass(lib, dtype, d, hd, ffn, layers, bytes_min):
+    """A workspace that holds the decode buffers alone is accepted (creation
+    then stops at the first device call); one byte less is an argument error."""
+    from paper_2606_03113_amd import lede
+    m = shrink(TINY, dtype=dtype, d_model=d, n_heads=4, n_kv_heads=4, head_dim=hd, ffn_dim=ffn, n_layers=layers,
+               vocab=1024 if d == 256 else 4096, exits=tuple(range(1, layers + 1)))
+    cfg = lede.make_config(m, 448, None, 8)
+    wb, kvb, wsb = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
+    assert lib.lede_region_bytes(ctypes.byref(cfg), ctypes.byref(wb), ctypes.byref(kvb), ctypes.byref(wsb)) == 0
+    assert wsb.value > bytes_min
+    for size, rc in ((wsb.value, lede.LEDE_E_HIP), (wsb.value - 1, lede.LEDE_E_HIP), (bytes_min, lede.LEDE_E_HIP),
+                     (bytes_min - 1, lede.LEDE_E_ARG)):
+        out = ctypes.c_void_p()
+        assert lib.lede_create(ctypes.byref(cfg), 256, wb.value, 256, kvb.value, 256, size, ctypes.byref(out)) == rc, size

@@ -3,6 +3,8 @@ the verify passes' kernels, which the oracle tests cover.  Both must leave the
 same bits: a prompt taken at once against the same prompt taken in pieces of
 at most 16 tokens, on the pages of a permuted pool, compared on the logits, the
 next token and the whole KV pool."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -190,3 +192,32 @@ def test_overflowed_value_stays_with_its_rows(ffn):
         clean = at_once[:, 0, :bad // 16 * 16]
         assert np.isfinite(pieces[:, 0, :bad // 16 * 16]).all()
         assert np.array_equal(clean, pieces[:, 0, :bad // 16 * 16])
+
+
+@pytest.mark.parametrize("model", [TINY, BF16_128], ids=lambda m: m.name)
+def test_smaller_workspaces(model):
+    """Workspaces that hold fewer rows of a prefill pass, in the end none: the
+    same bits (other pass sizes, and 16-row passes)."""
+    toks = li.uniform_int(1, 20, 440, 0, model.vocab - 1)
+    min_bytes = {"tiny": 500992, "bf16-hd128": 1207552}[model.name]
+    got = []
+    for share in (1.0, 0.5, 0.3, 0.0):
+        eng = _engine(model, 448, 1)
+        size = min_bytes + int(share * (eng.region_bytes[2] - min_bytes))
+        say("wide prefill, workspace of", size, "of", eng.region_bytes[2])
+        eng.L.lede_destroy(eng.ctx)
+        ctx = ctypes.c_void_p()
+        wb, kvb, _ = eng.region_bytes
+        eng.ws.fill_(0xFF)
+        assert eng.L.lede_create(ctypes.byref(eng.cfg), eng.weights.data_ptr(), wb, eng.kv.data_ptr(), kvb,
+                                 eng.ws.data_ptr(), size, ctypes.byref(ctx)) == 0
+        eng.ctx = ctx
+        eng.lede_set_options(0, 1)
+        eng.lede_prefill(toks[:300])
+        eng.lede_prefill(toks[300:])
+        got.append(_state(eng))
+        assert (eng.ws[size:] == 0xFF).all()
+        eng.close()
+    for state in got[1:]:
+        assert state[:3] == got[0][:3]
+        assert np.array_equal(state[3], got[0][3]) and np.array_equal(state[4], got[0][4])
