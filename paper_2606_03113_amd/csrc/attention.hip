@@ -504,11 +504,8 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
   const int tid = threadIdx.x, l = tid & 63, lr = l & 15, lg = l >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.nq / a.nkv, R = a.M * G, n_rb = (R + 16 * NW - 1) / (16 * NW);
-  // a KV head's row blocks run on one XCD (blocks b, b + 8, ...), whose L2
-  // then holds its pages; the longest first
-  const int jx = blockIdx.x >> 3;
-  const int kvh = (jx / n_rb) * 8 + (blockIdx.x & 7), rb = n_rb - 1 - jx % n_rb;
-  if (kvh >= a.nkv) return;
+  int kvh, rb;
+  attn_wide_block(blockIdx.x, a.nkv, n_rb, kvh, rb);
   const int pos0 = *a.seq_len + a.pos_off;
   const int r0 = rb * 16 * NW + 16 * w, rr = min(r0 + lr, R - 1);
   const bool row_ok = r0 + lr < R;
@@ -786,7 +783,7 @@ void plan_attention_wide(AttnArgs& a, int n_pos, size_t part_bytes) {
 
 hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s) {
   const int rows = a.M * (a.nq / a.nkv), n_rb = (rows + 127) / 128;
-  const dim3 grid(8 * ((a.nkv + 7) / 8) * n_rb, a.wide_split ? a.n_split : 1);
+  const dim3 grid(a.nkv * n_rb, a.wide_split ? a.n_split : 1);
   const int lds = 2 * (a.hd / 8) * 1024 + (2 * a.hd + 8 * 2 * 16) * 36 * 4;
   static const void* const kernels[2][3] = {
       {(const void*)k_attn_wide<64, 0>, (const void*)k_attn_wide<64, 1>, (const void*)k_attn_wide<64, 2>},

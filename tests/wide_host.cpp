@@ -11,4 +11,9 @@ void walk(int KT, int* tiles) {
   tiles[KT] = w.t;
 }
 
+// (KV head, row block) of each of an attention launch's nkv * n_rb blocks.
+void attn_blocks(int nkv, int n_rb, int* out) {
+  for (int b = 0; b < nkv * n_rb; ++b) lede::attn_wide_block(b, nkv, n_rb, out[2 * b], out[2 * b + 1]);
+}
+
 }
