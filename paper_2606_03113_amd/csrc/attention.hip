@@ -705,7 +705,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
 #pragma unroll
           for (int d = 0; d < 4; ++d)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ga[d0 + d][i] = fmaf(oc[d][i], sn, ga[d0 + d][i] * so);
+            for (int i = 0; i < 4; ++i) {
+              // (weights of 0 make an infinite value that other rows see a NaN)
+              const float o = masked && !in ? 0.f : oc[d][i];
+              ga[d0 + d][i] = fmaf(o, sn, ga[d0 + d][i] * so);
+            }
         }
       };
       if (ends) weigh(std::true_type{});

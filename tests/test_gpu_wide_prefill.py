@@ -159,17 +159,21 @@ def test_page_of_overflowed_scores(ffn):
     assert np.array_equal(got[0][4], got[1][4]) and np.array_equal(got[0][3], got[1][3])
 
 
+# (cached, new tokens, the bad one, rows before it that must be clean): a token
+# in a later group of 16 rows than the clean ones; and one in the same group,
+# which crosses a page, with the clean rows on the page before
+@pytest.mark.parametrize("ctx,n,bad,clean", [(0, 100, 57, 48), (128, 40, 153, 144), (180, 40, 194, 192)])
 @pytest.mark.parametrize("ffn", [256, 264], ids=["split", "unsplit"])
-def test_overflowed_value_stays_with_its_rows(ffn):
-    """A token whose value overflows to infinity: the rows of earlier groups of
-    16 in its page, which do not see it, keep the bits they have in 16-row
-    passes (a weight of 0 would make infinity a NaN)."""
+def test_overflowed_value_stays_with_its_rows(ffn, ctx, n, bad, clean):
+    """A token whose value overflows to infinity: the rows that do not see it,
+    of earlier groups of 16 in its page and of earlier pages in its group, keep
+    the bits they have in 16-row passes (a weight of 0 would make infinity a
+    NaN)."""
     from paper_2606_03113_amd import Engine
-    n, bad = 100, 57
     m = shrink(TINY, name="overflow-v", n_layers=2, n_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=ffn, dtype="bf16",
                qnet_hidden=32, exits=(1, 2))
     bf16 = lambda x: int(np.float32(x).view(np.uint32) >> 16)  # noqa: E731
-    toks = li.uniform_int(1, 20, n, 0, m.vocab - 2)
+    toks = li.uniform_int(1, 20, ctx + n, 0, m.vocab - 2)
     toks[bad] = m.vocab - 1
     w = li.weights(m)
     w["embed"][:, 1] = 0
@@ -177,21 +181,22 @@ def test_overflowed_value_stays_with_its_rows(ffn):
     w["layers"][0]["wv"][:, 1] = bf16(3e38)
     got = []
     for step in (n, 16):
-        say("wide prefill, overflowed value", ffn, step)
-        eng = Engine(m, max_ctx=128, k_max=8)
+        say("wide prefill, overflowed value", ffn, ctx, step)
+        eng = Engine(m, max_ctx=256, k_max=8)
         eng.kv.zero_()
         eng.load_weights(w, li.qnet_weights(m))
-        for i in range(0, n, step):
-            eng.lede_prefill(toks[i:min(n, i + step)])
-        half = eng.region_bytes[1] // 2
-        got.append([eng.kv[h:h + 2 * 2 * 64 * 64 * 2].view(torch.bfloat16).view(2, 2, 64, 64).float().cpu().numpy()
+        if ctx:
+            eng.lede_prefill(toks[:ctx])
+        for i in range(ctx, ctx + n, step):
+            eng.lede_prefill(toks[i:min(ctx + n, i + step)])
+        half, slots = eng.region_bytes[1] // 2, eng.cfg.n_pages * 64
+        got.append([eng.kv[h:h + 2 * slots * 64 * 2].view(torch.bfloat16).view(2, slots, 64).float().cpu().numpy()
                     for h in (0, half)])
         eng.close()
-    assert np.isinf(got[0][1][0, 0, bad]).all()
+    assert np.isinf(got[0][1][0, bad]).all()
     for at_once, pieces in zip(*got):
-        clean = at_once[:, 0, :bad // 16 * 16]
-        assert np.isfinite(pieces[:, 0, :bad // 16 * 16]).all()
-        assert np.array_equal(clean, pieces[:, 0, :bad // 16 * 16])
+        assert np.isfinite(pieces[:, :clean]).all()
+        assert np.array_equal(at_once[:, :clean], pieces[:, :clean])
 
 
 @pytest.mark.parametrize("model", [TINY, BF16_128], ids=lambda m: m.name)
