@@ -1,14 +1,16 @@
-"""The allocation-free sampling entry point (lede_op_sample_noalloc) against
-lede_op_sample, row by row, through the C ABI: two calls in a row on the
-same device array, the second with fewer and shorter rows, and a call with a
-row stride past the row length.  The draws are integers: bit-exact."""
+"""The allocation-free sampling entry point (lede_op_sample_noalloc) through the
+C ABI: its draws against the oracle's probabilities, with rows of up to and past
+the 32768 tokens that are read once; and, bit-exact, against lede_op_sample row
+by row: two calls in a row on the same device array, the second with fewer and
+shorter rows, and a call with a row stride past the row length."""
 import ctypes
 
 import numpy as np
 import pytest
 
 import lede_inputs as li
-from tests.parity import say
+from oracle import model as om
+from tests.parity import CDF_EPS, draw_consistent, say
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -32,6 +34,18 @@ def test_noalloc_sampling_matches_allocating_entry_point():
         u = li.uniform01(seed, 71, n)
         got = op_sample_noalloc(z, T, u)
         assert got == _reference(z, T, u)
+
+
+@pytest.mark.parametrize("n,V", [(32, 16), (32, 1025), (20, 32768), (20, 32769), (7, 50257), (3, 128256), (2, 300000)])
+def test_noalloc_sampling_is_inverse_cdf(n, V):
+    from paper_2606_03113_amd import op_sample_noalloc
+    say("noalloc sampling, oracle probabilities, rows=%d V=%d" % (n, V))
+    z = _rows(n, V, 5, 1.0)
+    u = li.uniform01(5, 74, n)
+    got = op_sample_noalloc(z, 0.6, u)
+    for r in range(n):
+        p = om.probs_at(z[r].cpu().numpy().astype(np.float64), 0.6)
+        assert draw_consistent(p, got[r], float(np.float32(u[r])), CDF_EPS), r
 
 
 def test_noalloc_row_stride_and_limits():
