@@ -10,10 +10,6 @@ namespace lede {
 
 // ---- attention over the paged KV cache --------------------------------------
 
-// At most this many thread groups in the combine kernel (16 pages each per
-// round of loads); a launch uses ceil(max_chunks / 16) of them.
-constexpr int COMBINE_GROUPS = 8;
-
 // Eight consecutive cache elements as fp32.
 template <int DT>
 __device__ __forceinline__ void load8(const void* base, size_t idx, float* o) {
@@ -752,37 +748,6 @@ __global__ __launch_bounds__(512, 2) void k_attn_wide(AttnArgs a) {
       store4<1>((uint8_t*)a.out + tiled_row_off<1>(m_row, head * HD + 16 * d + 4 * lg, a.KT_tiled), 0,
                 make_float4(ta[d][0] / tl, ta[d][1] / tl, ta[d][2] / tl, ta[d][3] / tl));
   }
-}
-
-// How a prefill pass's pages are split, at n_pos positions in all: the pass's
-// time is the chain of a block's pages, 2.7 us each, and, where they are split,
-// 4 us for a second launch and the partials' way through memory at 4 TB/s.
-// Partials of every page, split so that no CU gets two blocks, or of the
-// combine's groups; part_bytes bounds them.  The estimate has to win by a
-// tenth: at 64 to 200 cached positions (three to five pages) both ways take
-// the same time within 0.5 %.
-void plan_attention_wide(AttnArgs& a, int n_pos, size_t part_bytes) {
-  const int rows = a.M * (a.nq / a.nkv), blocks = a.nkv * ((rows + 127) / 128);
-  const int P = (n_pos + 63) / 64, S = (a.max_chunks + 15) / 16 < COMBINE_GROUPS ? (a.max_chunks + 15) / 16 : COMBINE_GROUPS;
-  const int used = (P + 15) / 16 < S ? (P + 15) / 16 : S;  // groups that have pages
-  const double part_mb = (double)a.M * a.nq * (a.hd + 2) * 4 * 1e-6;  // of one partial
-  double best = 2.7 * P * ((blocks + 255) / 256);
-  a.wide_split = 0;
-  auto consider = [&](int split, int n_blocks, int n_parts, int chain, int pages) {
-    const double t = 1.1 * (2.7 * chain * ((blocks * n_blocks + 255) / 256) + 4 + 2 * part_mb * n_parts / 4);
-    if (part_mb * 1e6 * n_parts > (double)part_bytes || t >= best) return;
-    best = t;
-    a.wide_split = split;
-    a.n_parts = n_parts;
-    a.pages_per_block = pages;
-    a.n_split = n_blocks;
-  };
-  const int per = 256 / blocks;  // blocks that a row block's pages may go to
-  if (per >= 2) {
-    const int pages = (P + per - 1) / per;
-    consider(1, (P + pages - 1) / pages, P, pages, pages);
-  }
-  if (used >= 2) consider(2, used, used, ((P + 15) / 16 + S - 1) / S * 16, 0);
 }
 
 hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s) {

@@ -155,8 +155,8 @@ struct DqnActArgs {
 hipError_t launch_norm(int dtype, const NormArgs& a, hipStream_t s);
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s);
 // Any number of rows (bf16, tiled output): the bits of launch_attention's
-// matrix-core path.
-void plan_attention_wide(AttnArgs& a, int n_pos, size_t part_bytes);
+// matrix-core path.  wide_split and what goes with it come from plan_attention_wide
+// (wide.h).
 hipError_t launch_attention_wide(const AttnArgs& a, hipStream_t s);
 hipError_t launch_qnet_out(const QnetOutArgs& a, hipStream_t s);
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t s);

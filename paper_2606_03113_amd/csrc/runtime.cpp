@@ -24,7 +24,6 @@ namespace {
 
 constexpr int PAGE = 64;
 constexpr int MROWS = 16;   // rows of one verify / prefill pass
-constexpr int WIDE_ROWS = 2048;  // rows of one prefill pass of the many-row kernels, at most
 static_assert(MROWS <= KEY_PITCH && 15 + 2 <= KEY_PITCH, "a key buffer holds every row's key and every draft's");
 constexpr int RECORD_INTS = 64;
 constexpr int UNIF_FLOATS = 2 * SAMPLE_SLOTS + 1;  // uniforms of a sampled step
@@ -158,7 +157,7 @@ Layout make_layout(const lede_config* c) {
   o.trace_bak = take((POLICY_TRACE + 2) * 4);
   o.pol_out = take((size_t)(c->n_exits + POLICY_MAX_DRAFT) * POLICY_LOG * 4);
   o.wide0 = off;
-  place_wide(o, std::min(WIDE_ROWS, (o.max_ctx + WIDE_ROW_PAD - 1) / WIDE_ROW_PAD * WIDE_ROW_PAD));
+  place_wide(o, wide_rows(o.max_ctx));
 
   o.kv_half = align256((size_t)o.L * o.n_pages * o.nkv * PAGE * o.hd * o.es);
   o.kvbytes = 2 * o.kv_half;
@@ -747,11 +746,10 @@ int run_wide(lede_ctx* c, int M, const int32_t* tokens, int pos_off, bool head, 
       at.q = c->S<float>(o.wq);
       at.out = c->S<uint8_t>(o.wattn); at.KT_tiled = KTq;
       const int n_pos = c->seq_len + pos_off + M;
-      // partials, where there are any, lie in the activations' rows, which
-      // hold nothing here (the zeros past F in a last tile that is not full
-      // have to stay: no partials then)
       at.part = c->S<float>(o.wact);
-      plan_attention_wide(at, n_pos, (size_t)KTf * TILE_BYTES == (size_t)o.F * 16 * o.es ? (size_t)o.wide_rows / 16 * KTf * TILE_BYTES : 0);
+      const AttnPlan plan = plan_attention_wide(M, o.nq, o.nkv, o.hd, o.max_chunks, n_pos, attn_part_room(o.wide_rows, o.F));
+      at.wide_split = plan.split; at.n_split = plan.n_blocks;
+      at.n_parts = plan.n_parts; at.pages_per_block = plan.pages_per_block;
       LAUNCH(LEDE_K_ATTENTION, (double)n_pos * o.kvd * 2.0 * o.es + 2.0 * M * o.qd * 4, launch_attention_wide(at, s));
     } else {
       for (int r = 0; r < M; r += MROWS) {

@@ -34,6 +34,12 @@ struct KWalk {
 };
 
 constexpr int WIDE_ROW_PAD = 128;  // row buffers hold a multiple of this many rows
+constexpr int WIDE_ROWS = 2048;    // rows of one prefill pass, at most
+// Rows that a context's workspace holds, unless it is a smaller one.
+inline int wide_rows(int max_ctx) {
+  const int rows = (max_ctx + WIDE_ROW_PAD - 1) / WIDE_ROW_PAD * WIDE_ROW_PAD;
+  return rows < WIDE_ROWS ? rows : WIDE_ROWS;
+}
 
 struct WideArgs {
   const uint8_t* w;    // tiled weights
@@ -74,6 +80,34 @@ struct HeadRowsArgs {
   const float* ss; float* ss_out; int groups;
 };
 
+// Which kernel a launch takes, by the columns and rows of a block's outputs:
+// 32 x 64 (k_wide), or 128 x 64, 64 x 64, 96 x 128 or 128 x 128 (k_wide_lds).
+// The one with the least estimated time on 256 CUs, from the tile
+// area per block and each kernel's rate when every CU is busy (TFLOP/s measured
+// at 2048 rows of the Llama-2-13B widths, 512 rows for the smaller tiles; two
+// blocks of any of them fit a CU).  A lone block on a CU runs at about 0.65 of
+// the CU's rate.  Smaller tiles win where larger ones leave CUs idle: at 512
+// rows, N = K = 4096, 64 x 64 tiles take 36 us against 40 for 128 x 64, 46 for
+// 96 x 128, 49 for 128 x 128 and 39 for the 32 x 64 tiles of k_wide; at
+// N = 22016, 188, 131, 114, 119 and 190; at 97 rows, N = 28672, 65, 47, 53, 49
+// and 61.  The fp32 models are small: they take two of the shapes.
+inline int wide_shape(int dtype, int n_groups, int M) {
+  struct Shape { int n, m; double rate; };
+  static const Shape shapes[5] = {{32, 64, 470.}, {128, 64, 720.}, {64, 64, 560.}, {96, 128, 840.}, {128, 128, 900.}};
+  int best = 0;
+  double best_t = 0.;
+  for (int i = 0; i < (dtype == 1 ? 5 : 2); ++i) {
+    const Shape& p = shapes[i];
+    const int blocks = ((n_groups * 16 + p.n - 1) / p.n) * ((M + p.m - 1) / p.m), load = (blocks + 255) / 256;
+    const double t = load * p.n * p.m / (p.rate * (load < 2 ? 0.65 : 1.));
+    if (i == 0 || t < best_t) {
+      best = i;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
 // Prefill attention: the KV head and row block of block b of nkv * n_rb.  Blocks
 // b, b + 8, ... run on one XCD.  Of each eight heads one runs on each XCD, whose
 // L2 then holds its pages; what is left over eight is dealt to all XCDs in turn,
@@ -90,6 +124,53 @@ __host__ __device__ inline void attn_wide_block(int b, int nkv, int n_rb, int& k
     kvh = full + (b - full * n_rb) % rem;
     rb = n_rb - 1 - (b - full * n_rb) / rem;
   }
+}
+
+// At most this many thread groups in the attention's combine kernel (16 pages
+// each per round of loads); a launch uses ceil(max_chunks / 16) of them.
+constexpr int COMBINE_GROUPS = 8;
+
+// How a prefill pass's pages are split, at n_pos positions in all: the pass's
+// time is the chain of a block's pages, 2.7 us each, and, where they are split,
+// 4 us for a second launch and the partials' way through memory at 4 TB/s.
+// Partials of every page, split so that no CU gets two blocks, or of the
+// combine's groups; part_bytes bounds them.  The estimate has to win by a
+// tenth: at 64 to 200 cached positions (three to five pages) both ways take
+// the same time within 0.5 %.
+struct AttnPlan {
+  int split = 0;                                  // 0 not split, 1 partials of pages, 2 of the combine's groups
+  int n_blocks = 1, n_parts = 0, pages_per_block = 0;  // per row block; per row and head; of mode 1
+};
+inline AttnPlan plan_attention_wide(int M, int nq, int nkv, int hd, int max_chunks, int n_pos, size_t part_bytes) {
+  const int rows = M * (nq / nkv), blocks = nkv * ((rows + 127) / 128);
+  const int P = (n_pos + 63) / 64, S = (max_chunks + 15) / 16 < COMBINE_GROUPS ? (max_chunks + 15) / 16 : COMBINE_GROUPS;
+  const int used = (P + 15) / 16 < S ? (P + 15) / 16 : S;  // groups that have pages
+  const double part_mb = (double)M * nq * (hd + 2) * 4 * 1e-6;  // of one partial
+  AttnPlan plan;
+  double best = 2.7 * P * ((blocks + 255) / 256);
+  auto consider = [&](int split, int n_blocks, int n_parts, int chain, int pages) {
+    const double t = 1.1 * (2.7 * chain * ((blocks * n_blocks + 255) / 256) + 4 + 2 * part_mb * n_parts / 4);
+    if (part_mb * 1e6 * n_parts > (double)part_bytes || t >= best) return;
+    best = t;
+    plan.split = split;
+    plan.n_blocks = n_blocks;
+    plan.n_parts = n_parts;
+    plan.pages_per_block = pages;
+  };
+  const int per = 256 / blocks;  // blocks that a row block's pages may go to
+  if (per >= 2) {
+    const int pages = (P + per - 1) / per;
+    consider(1, (P + pages - 1) / pages, P, pages, pages);
+  }
+  if (used >= 2) consider(2, used, used, ((P + 15) / 16 + S - 1) / S * 16, 0);
+  return plan;
+}
+
+// Where the partials of a split pass lie, and the bytes there (0: no splitting):
+// in the activations' rows, which hold nothing during attention, except where
+// zeros past F in a last tile that is not full have to stay.
+inline size_t attn_part_room(int rows, int F) {
+  return F % Tile<1>::TK == 0 ? (size_t)rows * F * Tile<1>::ES : 0;
 }
 
 hipError_t launch_wide(int dtype, WideArgs a, hipStream_t s);

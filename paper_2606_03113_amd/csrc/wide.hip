@@ -423,35 +423,14 @@ static hipError_t launch_staged(WideArgs& a, hipStream_t s) {
   return launch_tiles(f, a, WN * TN, WM * TM, WN * WM * 64, (size_t)S * (WN * TN + WM * TM) * TILE_BYTES, s);
 }
 
-// Which kernel: the one with the least estimated time on 256 CUs, from the tile
-// area per block and each kernel's rate when every CU is busy (TFLOP/s measured
-// at 2048 rows of the Llama-2-13B widths, 512 rows for the smaller tiles; two
-// blocks of any of them fit a CU).  A lone block on a CU runs at about 0.65 of
-// the CU's rate.  Smaller tiles win where larger ones leave CUs idle: at 512
-// rows, N = K = 4096, 64 x 64 tiles take 36 us against 40 for 128 x 64, 46 for
-// 96 x 128, 49 for 128 x 128 and 39 for the 32 x 64 tiles of k_wide; at
-// N = 22016, 188, 131, 114, 119 and 190; at 97 rows, N = 28672, 65, 47, 53, 49
-// and 61.  The fp32 models are small: they take two of the shapes.
 template <int DT>
 static hipError_t launch_dt(WideArgs& a, hipStream_t s) {
-  struct Shape { int n, m; double rate; };
-  static const Shape shapes[5] = {{32, 64, 470.}, {128, 64, 720.}, {64, 64, 560.}, {96, 128, 840.}, {128, 128, 900.}};
-  int best = 0;
-  double best_t = 0.;
-  for (int i = 0; i < (DT == 1 ? 5 : 2); ++i) {
-    const Shape& p = shapes[i];
-    const int blocks = ((a.n_groups * 16 + p.n - 1) / p.n) * ((a.M + p.m - 1) / p.m), load = (blocks + 255) / 256;
-    const double t = load * p.n * p.m / (p.rate * (load < 2 ? 0.65 : 1.));
-    if (i == 0 || t < best_t) {
-      best = i;
-      best_t = t;
-    }
-  }
-  if (best == 0) return launch_shape<DT, 2, 4, 2>(a, s);
-  if (best == 1) return launch_staged<DT, 4, 2, 2, 2, 5, 4>(a, s);
+  const int shape = wide_shape(DT, a.n_groups, a.M);
+  if (shape == 0) return launch_shape<DT, 2, 4, 2>(a, s);
+  if (shape == 1) return launch_staged<DT, 4, 2, 2, 2, 5, 4>(a, s);
   if (DT == 1) {
-    if (best == 2) return launch_staged<1, 2, 2, 2, 2, 8, 2>(a, s);
-    if (best == 3) return launch_staged<1, 3, 4, 2, 2, 5, 3>(a, s);
+    if (shape == 2) return launch_staged<1, 2, 2, 2, 2, 8, 2>(a, s);
+    if (shape == 3) return launch_staged<1, 3, 4, 2, 2, 5, 3>(a, s);
   }
   return launch_staged<1, 4, 4, 2, 2, 5, 1>(a, s);
 }

@@ -10,6 +10,7 @@ import pytest
 
 import lede_inputs as li
 from lede_inputs.configs import TINY, shrink
+from tests import wide_host
 from tests.parity import say
 
 pytestmark = pytest.mark.gpu
@@ -29,6 +30,26 @@ MODELS = [TINY, BF16_64, BF16_128, GQA_64, GQA_128_F32, GQA_8]
 # (tokens already cached, new tokens): one past a group, edges of row tiles and
 # pages, ragged ends, several page groups behind the rows
 SIZES = [(0, 17), (0, 64), (5, 65), (30, 127), (0, 129), (70, 300)]
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    return wide_host.load(tmp_path_factory.mktemp("wide_host"))
+
+
+def _shapes(host, m, n):
+    """Output tiles of n rows' linear kernels: QKV, output projection and down,
+    gate-up (0: k_wide; 1 to 4: k_wide_lds of 128 x 64, 64 x 64, 96 x 128, 128 x 128)."""
+    dt = int(m.dtype == "bf16")
+    return tuple(host.linear_shape(dt, g // 16, n) for g in (m.q_dim + 2 * m.kv_dim, m.d_model, 2 * m.ffn_dim))
+
+
+def _split(host, m, max_ctx, ctx, n):
+    """How the attention of n rows behind ctx positions is split (0: not, 1:
+    partials of pages, 2: of the combine's groups), and mode 1's pages per block."""
+    pages = ctypes.c_int()
+    mode = host.attn_split(m.n_heads, m.n_kv_heads, m.head_dim, m.ffn_dim, max_ctx, n, ctx + n, ctypes.byref(pages))
+    return mode, pages.value if mode == 1 else 0
 
 
 def _state(eng):
@@ -77,37 +98,55 @@ def test_prefill_of_several_passes(model):
     _check(model, 2400, 40, 2201)
 
 
+# every staged kernel with every epilogue, widths and row counts that end
+# inside a tile
+STAGED = shrink(TINY, name="bf16-staged", n_layers=1, d_model=4064, n_heads=33, n_kv_heads=11, head_dim=64,
+                ffn_dim=2008, vocab=512, dtype="bf16", qnet_hidden=32, exits=(1,))
+STAGED_F32 = shrink(STAGED, name="f32-staged", d_model=2080, n_heads=11, n_kv_heads=11, ffn_dim=1048, dtype="f32")
+
+
+@pytest.mark.parametrize("model,n,shape", [(STAGED, 947, 1), (STAGED, 441, 2), (STAGED, 1299, 3), (STAGED, 1793, 4),
+                                           (STAGED_F32, 1250, 1)], ids=lambda v: getattr(v, "name", v))
+def test_prefill_staged_kernels(host, model, n, shape):
+    assert _shapes(host, model, n) == (shape, shape, shape)
+    say("wide prefill, staged kernel", shape, model.name, n)
+    _check(model, 1856, 0, n)
+
+
 @pytest.mark.parametrize("model", [GQA_64, GQA_64_F], ids=lambda m: m.name)
-def test_prefill_past_128_pages(model):
+def test_prefill_past_128_pages(host, model):
     """Contexts longer than one round of the page combine's eight groups,
     walked by one block per row block, and split over the groups."""
+    assert _split(host, model, 8400, 8190, 130)[0] == (0 if model is GQA_64 else 2)
     say("wide prefill, 130 pages", model.name)
     _check(shrink(model, n_layers=1, exits=(1,)), 8400, 8190, 130)
 
 
-@pytest.mark.parametrize("model,ctx,n", [(GQA_8, 1300, 30), (GQA_8, 2130, 130), (BF16_128, 1980, 17), (GQA_64_F, 1500, 260),
-                                         (GQA_64, 1500, 130)],
+@pytest.mark.parametrize("model,ctx,n,split", [(GQA_8, 1300, 30, (1, 1)), (GQA_8, 2130, 130, (2, 0)), (BF16_128, 1980, 17, (1, 1)),
+                                               (GQA_64_F, 1500, 260, (2, 0)), (GQA_64, 1500, 130, (0, 0))],
                          ids=lambda v: getattr(v, "name", v))
-def test_prefill_behind_many_pages(model, ctx, n):
+def test_prefill_behind_many_pages(host, model, ctx, n, split):
     """Few rows behind many pages: the pages are split over blocks, with
-    partials of pages (first and third) or of the combine's groups (second and
-    fourth); not where the feed-forward width leaves a tile partly empty (last)."""
+    partials of pages or of the combine's groups; not where the feed-forward
+    width leaves a tile partly empty (last)."""
+    assert _split(host, model, 2400, ctx, n) == split
     say("wide prefill, many pages", model.name, ctx, n)
     _check(model, 2400, ctx, n)
 
 
-@pytest.mark.parametrize("ctx,n", [(33, 40), (33, 200), (1000, 40)])
-def test_prefill_at_full_width(ctx, n):
+@pytest.mark.parametrize("ctx,n,split", [(33, 40, (0, 0)), (33, 200, (0, 0)), (1000, 40, (1, 3))])
+def test_prefill_at_full_width(host, ctx, n, split):
     """One layer at the Llama-2-7B widths (the last with blocks of three pages)."""
     from lede_inputs.configs import WORKLOADS
     m = shrink(WORKLOADS["llama2-7b"].model, n_layers=1, exits=(1,))
+    assert _split(host, m, 512 if ctx < 512 else 1100, ctx, n) == split
     say("wide prefill, 7B widths", ctx, n)
     _check(m, 512 if ctx < 512 else 1100, ctx, n)
 
 
 # widths of a single K tile (32 bf16 or 16 fp32 columns), with enough rows and
-# columns for the staged kernel: gate-up and QKV, then down, with the tile full
-# and partly filled
+# columns for the staged kernel: gate-up, then down, with the tile full and
+# partly filled
 K1 = dict(n_layers=2, n_heads=2, n_kv_heads=1, head_dim=64, vocab=512, qnet_hidden=32, exits=(1, 2))
 K1_MODELS = [(shrink(TINY, name="bf16-d32", d_model=32, ffn_dim=1376, dtype="bf16", **K1), 600),
              (shrink(TINY, name="bf16-f32", d_model=4096, ffn_dim=32, dtype="bf16", **K1), 420),
@@ -116,22 +155,23 @@ K1_MODELS = [(shrink(TINY, name="bf16-d32", d_model=32, ffn_dim=1376, dtype="bf1
 
 
 @pytest.mark.parametrize("model,n", K1_MODELS, ids=lambda v: getattr(v, "name", v))
-def test_prefill_of_one_k_tile(model, n):
+def test_prefill_of_one_k_tile(host, model, n):
+    assert _shapes(host, model, n)[2 if model.d_model == 32 else 1] > 0
     say("wide prefill, one K tile", model.name, n)
     _check(model, 768, 0, n)
 
 
-@pytest.mark.parametrize("ffn", [256, 264], ids=["split", "unsplit"])
-def test_page_of_overflowed_scores(ffn):
+@pytest.mark.parametrize("heads,n,split", [(2, 40, 1), (32, 60, 0)], ids=["split", "unsplit"])
+def test_page_of_overflowed_scores(host, heads, n, split):
     """Cached keys so large that every score of a page overflows to -inf: the
     page has no weight, as in the 16-row kernels.  Every query has a large
     element in a slowly rotating dimension, in which the second page's keys
-    hold -3e38; with the feed-forward width a multiple of a tile the pages are
-    split over blocks."""
+    hold -3e38."""
     from paper_2606_03113_amd import Engine
-    hd, ctx, n = 64, 128, 40
-    m = shrink(TINY, name="overflow", n_layers=2, n_heads=2, n_kv_heads=1, head_dim=hd, ffn_dim=ffn, dtype="bf16",
+    hd, ctx = 64, 128
+    m = shrink(TINY, name="overflow", n_layers=2, n_heads=heads, n_kv_heads=1, head_dim=hd, ffn_dim=256, dtype="bf16",
                qnet_hidden=32, exits=(1, 2))
+    assert _split(host, m, 256, ctx, n)[0] == split
     bf16 = lambda x: int(np.float32(x).view(np.uint32) >> 16)  # noqa: E731
     w = li.weights(m)
     w["embed"][:, 0] = bf16(0.08)
@@ -140,7 +180,7 @@ def test_page_of_overflowed_scores(ffn):
     toks = li.uniform_int(1, 20, ctx + n, 0, m.vocab - 1)
     got = []
     for step in (n, 16):
-        say("wide prefill, overflowed scores", ffn, step)
+        say("wide prefill, overflowed scores", heads, step)
         eng = Engine(m, max_ctx=256, k_max=8)
         eng.kv.zero_()
         eng.load_weights(w, li.qnet_weights(m))
@@ -159,19 +199,22 @@ def test_page_of_overflowed_scores(ffn):
     assert np.array_equal(got[0][4], got[1][4]) and np.array_equal(got[0][3], got[1][3])
 
 
-# (cached, new tokens, the bad one, rows before it that must be clean): a token
-# in a later group of 16 rows than the clean ones; and one in the same group,
-# which crosses a page, with the clean rows on the page before
-@pytest.mark.parametrize("ctx,n,bad,clean", [(0, 100, 57, 48), (128, 40, 153, 144), (180, 40, 194, 192)])
-@pytest.mark.parametrize("ffn", [256, 264], ids=["split", "unsplit"])
-def test_overflowed_value_stays_with_its_rows(ffn, ctx, n, bad, clean):
+# query heads, cached, new tokens, the bad one, rows before it that must be
+# clean, and how the pages are split: a token in a later group of 16 rows than
+# the clean ones; and one in the same group, which crosses a page, with the
+# clean rows on the page before
+@pytest.mark.parametrize("heads,ctx,n,bad,clean,split", [(2, 0, 100, 57, 48, 0), (2, 52, 40, 66, 64, 0), (2, 128, 40, 153, 144, 1),
+                                                         (2, 180, 40, 194, 192, 1), (8, 1972, 40, 1986, 1984, 2)])
+def test_overflowed_value_stays_with_its_rows(host, heads, ctx, n, bad, clean, split):
     """A token whose value overflows to infinity: the rows that do not see it,
     of earlier groups of 16 in its page and of earlier pages in its group, keep
     the bits they have in 16-row passes (a weight of 0 would make infinity a
     NaN)."""
     from paper_2606_03113_amd import Engine
-    m = shrink(TINY, name="overflow-v", n_layers=2, n_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=ffn, dtype="bf16",
+    max_ctx = 2048 if ctx > 256 else 256
+    m = shrink(TINY, name="overflow-v", n_layers=2, n_heads=heads, n_kv_heads=1, head_dim=64, ffn_dim=256, dtype="bf16",
                qnet_hidden=32, exits=(1, 2))
+    assert _split(host, m, max_ctx, ctx, n)[0] == split
     bf16 = lambda x: int(np.float32(x).view(np.uint32) >> 16)  # noqa: E731
     toks = li.uniform_int(1, 20, ctx + n, 0, m.vocab - 2)
     toks[bad] = m.vocab - 1
@@ -181,8 +224,8 @@ def test_overflowed_value_stays_with_its_rows(ffn, ctx, n, bad, clean):
     w["layers"][0]["wv"][:, 1] = bf16(3e38)
     got = []
     for step in (n, 16):
-        say("wide prefill, overflowed value", ffn, ctx, step)
-        eng = Engine(m, max_ctx=256, k_max=8)
+        say("wide prefill, overflowed value", heads, ctx, step)
+        eng = Engine(m, max_ctx=max_ctx, k_max=8)
         eng.kv.zero_()
         eng.load_weights(w, li.qnet_weights(m))
         if ctx:
