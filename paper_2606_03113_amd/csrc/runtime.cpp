@@ -746,8 +746,9 @@ int run_wide(lede_ctx* c, int M, const int32_t* tokens, int pos_off, bool head, 
       at.q = c->S<float>(o.wq);
       at.out = c->S<uint8_t>(o.wattn); at.KT_tiled = KTq;
       const int n_pos = c->seq_len + pos_off + M;
-      at.part = c->S<float>(o.wact);
-      const AttnPlan plan = plan_attention_wide(M, o.nq, o.nkv, o.hd, o.max_chunks, n_pos, attn_part_room(o.wide_rows, o.F));
+      const AttnRoom room = attn_part_room(o.wide_rows, o.max_chunks, o.nq, o.hd, o.d, o.F);
+      at.part = c->S<float>(room.at == PART_ACT ? o.wact : room.at == PART_NORM ? o.wxn : o.part);
+      const AttnPlan plan = plan_attention_wide(M, o.nq, o.nkv, o.hd, o.max_chunks, n_pos, room.bytes);
       at.wide_split = plan.split; at.n_split = plan.n_blocks;
       at.n_parts = plan.n_parts; at.pages_per_block = plan.pages_per_block;
       LAUNCH(LEDE_K_ATTENTION, (double)n_pos * o.kvd * 2.0 * o.es + 2.0 * M * o.qd * 4, launch_attention_wide(at, s));

@@ -46,10 +46,13 @@ def _shapes(host, m, n):
 
 def _split(host, m, max_ctx, ctx, n):
     """How the attention of n rows behind ctx positions is split (0: not, 1:
-    partials of pages, 2: of the combine's groups), and mode 1's pages per block."""
-    pages = ctypes.c_int()
-    mode = host.attn_split(m.n_heads, m.n_kv_heads, m.head_dim, m.ffn_dim, max_ctx, n, ctx + n, ctypes.byref(pages))
-    return mode, pages.value if mode == 1 else 0
+    partials of pages, 2: of the combine's groups), mode 1's pages per block,
+    and where the partials lie (0: the 16-row passes', 1: the normalised rows',
+    2: the activations' region)."""
+    pages, at = ctypes.c_int(), ctypes.c_int()
+    mode = host.attn_split(m.n_heads, m.n_kv_heads, m.head_dim, m.d_model, m.ffn_dim, max_ctx, n, ctx + n,
+                           ctypes.byref(pages), ctypes.byref(at))
+    return mode, pages.value if mode == 1 else 0, at.value if mode else None
 
 
 def _state(eng):
@@ -113,28 +116,30 @@ def test_prefill_staged_kernels(host, model, n, shape):
     _check(model, 1856, 0, n)
 
 
-@pytest.mark.parametrize("model", [GQA_64, GQA_64_F], ids=lambda m: m.name)
-def test_prefill_past_128_pages(host, model):
+@pytest.mark.parametrize("model,n,split", [(GQA_64, 400, (0, 0, None)), (GQA_64, 130, (2, 0, 0)), (GQA_64_F, 130, (2, 0, 2))],
+                         ids=lambda v: getattr(v, "name", v))
+def test_prefill_past_128_pages(host, model, n, split):
     """Contexts longer than one round of the page combine's eight groups,
     walked by one block per row block, and split over the groups."""
-    assert _split(host, model, 8400, 8190, 130)[0] == (0 if model is GQA_64 else 2)
-    say("wide prefill, 130 pages", model.name)
-    _check(shrink(model, n_layers=1, exits=(1,)), 8400, 8190, 130)
+    assert _split(host, model, 8640, 8190, n) == split
+    say("wide prefill, 128 pages", model.name, n)
+    _check(shrink(model, n_layers=1, exits=(1,)), 8640, 8190, n)
 
 
-@pytest.mark.parametrize("model,ctx,n,split", [(GQA_8, 1300, 30, (1, 1)), (GQA_8, 2130, 130, (2, 0)), (BF16_128, 1980, 17, (1, 1)),
-                                               (GQA_64_F, 1500, 260, (2, 0)), (GQA_64, 1500, 130, (0, 0))],
+@pytest.mark.parametrize("model,ctx,n,split", [(GQA_8, 1300, 30, (1, 1, 2)), (GQA_8, 2130, 130, (2, 0, 2)),
+                                               (BF16_128, 1980, 17, (1, 1, 2)), (GQA_64_F, 1500, 260, (2, 0, 2)),
+                                               (GQA_64, 1500, 130, (2, 0, 1)), (GQA_64, 2000, 17, (1, 1, 1))],
                          ids=lambda v: getattr(v, "name", v))
 def test_prefill_behind_many_pages(host, model, ctx, n, split):
     """Few rows behind many pages: the pages are split over blocks, with
-    partials of pages or of the combine's groups; not where the feed-forward
-    width leaves a tile partly empty (last)."""
+    partials of pages or of the combine's groups, in the activations' region or,
+    where the feed-forward width leaves a tile partly empty, another."""
     assert _split(host, model, 2400, ctx, n) == split
     say("wide prefill, many pages", model.name, ctx, n)
     _check(model, 2400, ctx, n)
 
 
-@pytest.mark.parametrize("ctx,n,split", [(33, 40, (0, 0)), (33, 200, (0, 0)), (1000, 40, (1, 3))])
+@pytest.mark.parametrize("ctx,n,split", [(33, 40, (0, 0, None)), (33, 200, (0, 0, None)), (1000, 40, (1, 3, 2))])
 def test_prefill_at_full_width(host, ctx, n, split):
     """One layer at the Llama-2-7B widths (the last with blocks of three pages)."""
     from lede_inputs.configs import WORKLOADS

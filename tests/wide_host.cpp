@@ -19,12 +19,14 @@ void attn_blocks(int nkv, int n_rb, int* out) {
 // The kernel (index of its output tile) of a linear launch with M rows.
 int linear_shape(int dtype, int n_groups, int M) { return lede::wide_shape(dtype, n_groups, M); }
 
-// How an attention launch of M rows that ends at n_pos positions is split, and
-// the pages of a block in mode 1.
-int attn_split(int nq, int nkv, int hd, int F, int max_ctx, int M, int n_pos, int* pages) {
-  const lede::AttnPlan p = lede::plan_attention_wide(M, nq, nkv, hd, (max_ctx + 63) / 64, n_pos,
-                                                     lede::attn_part_room(lede::wide_rows(max_ctx), F));
+// How an attention launch of M rows that ends at n_pos positions is split; the
+// pages of a block in mode 1, and where the partials lie.
+int attn_split(int nq, int nkv, int hd, int d, int F, int max_ctx, int M, int n_pos, int* pages, int* at) {
+  const int chunks = (max_ctx + 63) / 64;
+  const lede::AttnRoom room = lede::attn_part_room(lede::wide_rows(max_ctx), chunks, nq, hd, d, F);
+  const lede::AttnPlan p = lede::plan_attention_wide(M, nq, nkv, hd, chunks, n_pos, room.bytes);
   *pages = p.pages_per_block;
+  *at = room.at;
   return p.split;
 }
 
