@@ -29,7 +29,7 @@ struct AttnArgs {
   const int32_t* block_table; const int32_t* seq_len; int pos_off;
   int n_split;                     // blocks per (kv head, row slice); chunks strided
   int rows_per_block;              // <= 16 query rows (m, head-in-group) per block
-  int short_ctx;                   // at most 16 pages, all taken by one block per (kv head, row slice), which folds them itself (n_split 1)
+  int short_ctx;                   // a context of one page (two for one row): one block per (kv head, row slice) folds them itself (n_split 1)
   int max_chunks;
   float* part;                     // [M][nq][max_chunks][hd + 2] (wide_split: [M][nq][n_parts][hd + 2])
   void* out; int ldo;              // combine output [M][nq*hd], model dtype

@@ -324,8 +324,8 @@ __device__ inline float2 group_row_stats(const float2* gs, int G, float inv_t, f
 // group whose running weight crosses u * total, then the token within it whose
 // running weight does (else, by rounding, the group's last token of positive
 // weight).  -1 when the total weight is 0; total receives it.
-__device__ int draw_group(const GroupChunk& ch, float s, const float* z, float mx, float inv_t, float u, float& total,
-                          float* red, int* ired) {
+__device__ inline int draw_group(const GroupChunk& ch, float s, const float* z, float mx, float inv_t, float u,
+                                 float& total, float* red, int* ired) {
   const float pre = block_excl_scan(s, red, total);
   const float thr = u * total;
   const int owner = block_max_i((s > 0.f && pre <= thr) ? (int)threadIdx.x : -1, ired);

@@ -87,10 +87,14 @@ struct HeadRowsArgs {
 // at 2048 rows of the Llama-2-13B widths, 512 rows for the smaller tiles; two
 // blocks of any of them fit a CU).  A lone block on a CU runs at about 0.65 of
 // the CU's rate.  Smaller tiles win where larger ones leave CUs idle: at 512
-// rows, N = K = 4096, 64 x 64 tiles take 36 us against 40 for 128 x 64, 46 for
-// 96 x 128, 49 for 128 x 128 and 39 for the 32 x 64 tiles of k_wide; at
-// N = 22016, 188, 131, 114, 119 and 190; at 97 rows, N = 28672, 65, 47, 53, 49
-// and 61.  The fp32 models are small: they take two of the shapes.
+// rows, N = K = 4096, 64 x 64 tiles take 39 us against 42 for 128 x 64, 51 for
+// 96 x 128, 54 for 128 x 128 and 47 for the 32 x 64 tiles of k_wide; at
+// N = 22016, 182, 143, 129, 120 and 211; at 97 rows, N = 28672, 77, 64, 78, 60
+// and 85.  Over the four launches of a layer at the Llama-2-7B and 13B and
+// Llama-3-8B widths with 33 to 2048 rows the choice is the best of the five or
+// within 2 % of it in 86 of 120 cases and within 10 % in 104; the worst is
+// 768 rows, N = 4096, K = 14336 (188 us, 146 with 128 x 128 tiles).  The fp32
+// models are small: they take two of the shapes.
 inline int wide_shape(int dtype, int n_groups, int M) {
   struct Shape { int n, m; double rate; };
   static const Shape shapes[5] = {{32, 64, 470.}, {128, 64, 720.}, {64, 64, 560.}, {96, 128, 840.}, {128, 128, 900.}};

@@ -239,8 +239,10 @@ __global__ __launch_bounds__(512) void k_wide(WideArgs a) {
 // reads have no bank conflicts).  While a K tile is multiplied, the next one's
 // operands are read into registers (all of them, or where three sets of
 // accumulators leave no room PF of the TN weight tiles) and later ones are
-// copied.  What is left over the products' time is the barrier per K tile
-// (70 ns of 410 for 256 x 128 outputs), the copies (70 ns) and 14 us a launch.
+// copied.  With two blocks of 128 x 128 outputs on every CU a K tile of both
+// takes 487 ns and a launch 17 us besides (2048 rows, N = 4096: 79, 185 and 235
+// us at K = 4096, 11008 and 14336), where the products alone would take 215 at
+// the matrix cores' peak; the rest is copies, LDS reads and the barrier per tile.
 template <int N>
 __device__ __forceinline__ void stage_barrier() {  // this wavefront's copies but the last N, and its LDS reads; then all
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
