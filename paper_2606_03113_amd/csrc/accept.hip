@@ -144,21 +144,16 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t s) {
-  if (!a.gstats)
-    if (const hipError_t e = allow_row_lds((const void*)k_sample)) return e;
   hipLaunchKernelGGL(k_sample, dim3(a.n_rows), dim3(SB), a.gstats ? 0 : ROW_LDS, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_row_stats(const RowStatsArgs& a, int rows, hipStream_t s) {
-  if (!a.gstats)
-    if (const hipError_t e = allow_row_lds((const void*)k_row_stats)) return e;
   hipLaunchKernelGGL(k_row_stats, dim3(rows), dim3(SB), a.gstats ? 0 : ROW_LDS, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_accept_sampled(const SampledAcceptArgs& a, hipStream_t s) {
-  if (const hipError_t e = allow_row_lds((const void*)k_accept_sampled)) return e;
   hipLaunchKernelGGL(k_accept_sampled, dim3(1), dim3(SB), ROW_LDS, s, a);
   return hipGetLastError();
 }

@@ -155,7 +155,6 @@ __global__ __launch_bounds__(64) void k_trace_push(TracePushArgs a) {
 }
 
 hipError_t launch_exit_policy(const ExitPolicyArgs& a, hipStream_t s) {
-  if (const hipError_t e = allow_row_lds((const void*)k_exit_policy)) return e;
   hipLaunchKernelGGL(k_exit_policy, dim3(1), dim3(SB), ROW_LDS, s, a);
   return hipGetLastError();
 }

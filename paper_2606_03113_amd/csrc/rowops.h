@@ -23,11 +23,6 @@ constexpr int SB = 1024, SW = SB / 64, CB = 16;
 constexpr int ROW_PITCH = CB + 4;                            // words between a batch's chunks in LDS
 constexpr int ROW_LDS = SB * ROW_PITCH * (int)sizeof(float);  // dynamic LDS of a kernel that reads rows
 
-// Dynamic LDS past 64 KiB has to be asked for, as for the many-row kernels.
-inline hipError_t allow_row_lds(const void* kernel) {
-  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, ROW_LDS);
-}
-
 __device__ __forceinline__ int chunk_len(int V) { return ((V + SB - 1) / SB + 3) / 4 * 4; }
 
 // Elements [j0, j0 + CB) of this thread's chunk of row z into r, zero past the
