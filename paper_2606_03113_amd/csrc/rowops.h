@@ -21,7 +21,10 @@ namespace lede {
 
 constexpr int SB = 1024, SW = SB / 64, CB = 16;
 constexpr int ROW_PITCH = CB + 4;                            // words between a batch's chunks in LDS
-constexpr int ROW_LDS = SB * ROW_PITCH * (int)sizeof(float);  // dynamic LDS of a kernel that reads rows
+// Dynamic LDS of a kernel that reads rows: half of the batches at a time, so that
+// a launch keeps to 64 KiB (asking for more takes the host 1 us a launch).
+constexpr int ROW_LDS = SB / 2 * ROW_PITCH * (int)sizeof(float);
+static_assert(ROW_LDS <= 48 * 1024, "and the kernels' own arrays, up to 13 KB");
 
 __device__ __forceinline__ int chunk_len(int V) { return ((V + SB - 1) / SB + 3) / 4 * 4; }
 
@@ -30,7 +33,7 @@ __device__ __forceinline__ int chunk_len(int V) { return ((V + SB - 1) / SB + 3)
 __device__ __forceinline__ void load_chunks(const float* z, int V, int C, int j0, float (&r)[CB]) {
   extern __shared__ __align__(16) float row_lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float* tb = row_lds + wave * 64 * ROW_PITCH;
+  float* tb = row_lds + wave * 32 * ROW_PITCH;
   const bool vec = ((uintptr_t)z & 15) == 0;
   const int part = j0 + 4 * (lane & 3);
   float4 v[4];
@@ -49,13 +52,17 @@ __device__ __forceinline__ void load_chunks(const float* z, int V, int C, int j0
       }
     }
   }
-  __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) *(float4*)&tb[(16 * i + (lane >> 2)) * ROW_PITCH + 4 * (lane & 3)] = v[i];
-  __builtin_amdgcn_wave_barrier();
+  for (int h = 0; h < 2; ++h) {  // the first 32 lanes' chunks, then the others'
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) *(float4*)&r[4 * i] = *(const float4*)&tb[lane * ROW_PITCH + 4 * i];
-  __builtin_amdgcn_wave_barrier();
+    for (int i = 0; i < 2; ++i) *(float4*)&tb[(16 * i + (lane >> 2)) * ROW_PITCH + 4 * (lane & 3)] = v[2 * h + i];
+    __builtin_amdgcn_wave_barrier();
+    if (lane >> 5 == h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *(float4*)&r[4 * i] = *(const float4*)&tb[(lane & 31) * ROW_PITCH + 4 * i];
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 // Elements of the batch at j0 that belong to this thread's chunk and the row.
 __device__ __forceinline__ int chunk_count(int V, int C, int j0) {
@@ -205,7 +212,7 @@ __device__ int block_draw(F f, const float* z1, const float* z2, int V, float u,
 // The row's maximum, and this thread's chunk sum of exp((z - max) * inv_t).
 // Rows of up to 2 CB SB tokens (chunks of at most 2 CB) are read once, and r
 // then holds the weights; rows of up to CB SB take one batch (a draw from 1000
-// tokens 37.2 us with its read-back, 40.8 with the exponentials of an empty
+// tokens 38.4 us with its read-back, 3 us more with the exponentials of an empty
 // second batch).
 __device__ inline float row_max_sum(const float* z, int V, float inv_t, float& s, float (&r)[2][CB], float* red) {
   const int C = chunk_len(V);
